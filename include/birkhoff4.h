@@ -133,6 +133,11 @@ int birkhoff4_fwd_ex2(const void* H, int h_dtype, float* P, float* dual, int32_t
 int birkhoff4_bwd_ex(const float* P, const void* dP, int dp_dtype, float* dH, int64_t B,
                      hipStream_t stream);
 
+/* Backward with storage dtypes for dP and for dH (BIRKHOFF4_F32 or BIRKHOFF4_BF16 each): a
+ * bf16 dH [B][4][4] is the fp32 gradient rounded to nearest even. */
+int birkhoff4_bwd_ex2(const float* P, const void* dP, int dp_dtype, void* dH, int dh_dtype,
+                      int64_t B, hipStream_t stream);
+
 /* Saved-Hessian variant (Sec. 4.2: at the solution the Hessian of the reduced dual equals
  * the Delta of eq. derivative, so the forward's Hessian can be kept for the backward).
  * birkhoff4_fwd_hess is birkhoff4_fwd_ex (one problem per lane, any B) that also writes,
@@ -185,6 +190,10 @@ int birkhoff8_fwd(const void* H, int h_dtype, float* P, float* dual, int32_t* it
  * reduced dual at P. Rows and columns of dH sum to zero. dH must not overlap P or dP. */
 int birkhoff8_bwd(const float* P, const void* dP, int dp_dtype, float* dH, int64_t B,
                   hipStream_t stream);
+
+/* birkhoff8_bwd with a storage dtype for dH (as in birkhoff4_bwd_ex2). */
+int birkhoff8_bwd_ex(const float* P, const void* dP, int dp_dtype, void* dH, int dh_dtype,
+                     int64_t B, hipStream_t stream);
 
 /* ---------------------------------------------------------------------------
  * General entropic OT for 4 x 4 (eq. entropic, Sec. 2.3): for each b,

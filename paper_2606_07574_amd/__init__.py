@@ -57,6 +57,7 @@ def _load():
         "birkhoff4_fwd_ex": [vp, i32, vp, vp, vp, i64, f32, i32, st],
         "birkhoff4_fwd_ex2": [vp, i32, vp, vp, vp, i64, f32, i32, i32, st],
         "birkhoff4_bwd_ex": [vp, vp, i32, vp, i64, st],
+        "birkhoff4_bwd_ex2": [vp, vp, i32, vp, i32, i64, st],
         "birkhoff4_fwd_hess": [vp, i32, vp, vp, vp, vp, i64, f32, i32, st],
         "birkhoff4_bwd_hess": [vp, vp, vp, i32, vp, i64, st],
         "birkhoff4_sk_fwd": [vp, i32, vp, i64, i32, st],
@@ -65,6 +66,7 @@ def _load():
         "birkhoff4_ot_fwd": [vp, vp, vp, f32, vp, vp, vp, i64, f32, i32, st],
         "birkhoff4_ot_bwd": [vp, vp, vp, f32, vp, i64, st],
         "birkhoff8_bwd": [vp, vp, i32, vp, i64, st],
+        "birkhoff8_bwd_ex": [vp, vp, i32, vp, i32, i64, st],
         "birkhoff8_ot_fwd": [vp, vp, vp, f32, vp, vp, vp, i64, f32, i32, st],
         "birkhoff8_ot_bwd": [vp, vp, vp, f32, vp, i64, st],
         "birkhoff4_mix_fwd": [vp, i32, vp, i32, vp, vp, vp, vp, i64, i64, f32, i32, st],
@@ -157,18 +159,24 @@ def fwd(H: torch.Tensor, tol: float = DEFAULT_TOL, max_iter: int = DEFAULT_MAX_I
     return P, dual, iters
 
 
-def bwd(P: torch.Tensor, dP: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tensor:
-    """dL/dH from P (the forward output) and dL/dP (float32 or bfloat16)."""
-    B = _batch(P, "P")
-    if _batch(dP, "dP") != B:
+def _bwd(n: int, P: torch.Tensor, dP: torch.Tensor, out: torch.Tensor | None, dtype: torch.dtype) -> torch.Tensor:
+    """dL/dH of the n x n projection, stored as dtype (float32 or bfloat16)."""
+    B = _batch(P, "P", n)
+    if _batch(dP, "dP", n) != B:
         raise ValueError("P and dP batch sizes differ")
     if P.dtype != torch.float32:
         raise TypeError("P must be float32")
     _same_device(P, dP)
-    dH = _out(out, P.shape, P.device)
+    dH = torch.empty(P.shape, dtype=dtype, device=P.device) if out is None else _out(out, P.shape, P.device)
+    fn = _load().birkhoff4_bwd_ex2 if n == 4 else _load().birkhoff8_bwd_ex
     with torch.cuda.device(P.device):
-        _check(_load().birkhoff4_bwd_ex(_ptr(P), _ptr(dP), _dtype_code(dP), _ptr(dH), B, _stream(P)))
+        _check(fn(_ptr(P), _ptr(dP), _dtype_code(dP), _ptr(dH), _dtype_code(dH), B, _stream(P)))
     return dH
+
+
+def bwd(P: torch.Tensor, dP: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tensor:
+    """dL/dH from P (the forward output) and dL/dP (float32 or bfloat16)."""
+    return _bwd(4, P, dP, out, torch.float32)
 
 
 def fwd_hess(H: torch.Tensor, tol: float = DEFAULT_TOL, max_iter: int = DEFAULT_MAX_ITER,
@@ -239,8 +247,8 @@ class Birkhoff4Fn(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dP):
         (P,) = ctx.saved_tensors
-        dH = bwd(P, dP.contiguous())
-        return dH.to(ctx.in_dtype), None, None
+        # the gradient in H's own dtype straight from the kernel: no conversion pass
+        return _bwd(4, P, dP.contiguous(), None, ctx.in_dtype), None, None
 
 
 def project(H: torch.Tensor, tol: float = DEFAULT_TOL, max_iter: int = DEFAULT_MAX_ITER) -> torch.Tensor:
@@ -263,16 +271,7 @@ def fwd8(H: torch.Tensor, tol: float = DEFAULT_TOL, max_iter: int = DEFAULT_MAX_
 
 def bwd8(P: torch.Tensor, dP: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tensor:
     """bwd for trailing 8x8 matrices."""
-    B = _batch(P, "P", 8)
-    if _batch(dP, "dP", 8) != B:
-        raise ValueError("P and dP batch sizes differ")
-    if P.dtype != torch.float32:
-        raise TypeError("P must be float32")
-    _same_device(P, dP)
-    dH = _out(out, P.shape, P.device)
-    with torch.cuda.device(P.device):
-        _check(_load().birkhoff8_bwd(_ptr(P), _ptr(dP), _dtype_code(dP), _ptr(dH), B, _stream(P)))
-    return dH
+    return _bwd(8, P, dP, out, torch.float32)
 
 
 class Birkhoff8Fn(torch.autograd.Function):
@@ -288,8 +287,7 @@ class Birkhoff8Fn(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dP):
         (P,) = ctx.saved_tensors
-        dH = bwd8(P, dP.contiguous())
-        return dH.to(ctx.in_dtype), None, None
+        return _bwd(8, P, dP.contiguous(), None, ctx.in_dtype), None, None
 
 
 def project8(H: torch.Tensor, tol: float = DEFAULT_TOL, max_iter: int = DEFAULT_MAX_ITER) -> torch.Tensor:

@@ -900,22 +900,33 @@ __device__ __forceinline__ void implicit_vjp(const float T[16], const float G[16
 // consecutive problems), transposed through a per-wave LDS buffer to one problem per
 // lane. Per-lane 64-byte records (four 16-byte accesses at a 64-byte stride) stream at
 // about half the rate. Every byte is touched once, so all accesses carry the
-// non-temporal hint (measured 11 % faster on MI355X than default caching).
+// non-temporal hint (measured 11 % faster on MI355X than default caching). dH leaves as fp32
+// or, rounded to nearest even, as bf16 (DO): a program whose logits are bf16 needs their
+// gradient in bf16, and rounding it here instead of in a pass of its own takes 128 of the 288
+// bytes per problem away (2^24 problems, fp32 dP: forward + backward + conversion 1.184 ms,
+// forward + backward 0.861 ms).
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// Two values rounded to nearest even bf16 in one word (the hardware conversion).
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
+}
+
 constexpr int kBwdBlock = 256;
 constexpr int kBwdWaves = kBwdBlock / 64;
 constexpr int kBwdStride = 5;  // v4f per problem in the LDS buffer (4 rows + 1 pad: no bank conflicts on reads)
 
-template <int DT, bool HESS = false>
+template <int DT, int DO, bool HESS = false>
 __global__ __launch_bounds__(kBwdBlock) void implicit_bwd_kernel(const float* __restrict__ P,
                                                                   const void* __restrict__ dP,
-                                                                  float* __restrict__ dH, int64_t B,
+                                                                  void* __restrict__ dH, int64_t B,
                                                                   const float* __restrict__ hess) {
     __shared__ v4f buf_all[kBwdWaves][64 * kBwdStride];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     v4f* const buf = buf_all[wv];
     const v4f* P4 = reinterpret_cast<const v4f*>(P);
-    v4f* dH4 = reinterpret_cast<v4f*>(dH);
     // slot of the 16-byte piece this lane moves in a coalesced access q: problem 16 q + lane / 4, row lane % 4
     const int cpos = (lane >> 2) * kBwdStride + (lane & 3);
     const int64_t nchunk = (B + 63) / 64;
@@ -993,16 +1004,31 @@ __global__ __launch_bounds__(kBwdBlock) void implicit_bwd_kernel(const float* __
         } else {
             implicit_vjp(T, G, out);
         }
-        // dH: one problem per lane to pieces
+        // dH: one problem per lane to pieces, four per problem or (bf16) two
+        if constexpr (DO == BIRKHOFF4_BF16) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            buf[lane * kBwdStride + r] = v4f{out[4 * r], out[4 * r + 1], out[4 * r + 2], out[4 * r + 3]};
-        __builtin_amdgcn_wave_barrier();
+            for (int r = 0; r < 2; ++r)
+                bufu[lane * kBwdStride + r] =
+                    v4u{pack_bf16(out[8 * r], out[8 * r + 1]), pack_bf16(out[8 * r + 2], out[8 * r + 3]),
+                        pack_bf16(out[8 * r + 4], out[8 * r + 5]), pack_bf16(out[8 * r + 6], out[8 * r + 7])};
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int k = 64 * q + lane;
-            const v4f o = buf[16 * q * kBwdStride + cpos];
-            if (k < 4 * n) __builtin_nontemporal_store(o, dH4 + 4 * base + k);
+            for (int q = 0; q < 2; ++q) {
+                const int k = 64 * q + lane;
+                const v4u o = bufu[(k >> 1) * kBwdStride + (k & 1)];
+                if (k < 2 * n) __builtin_nontemporal_store(o, reinterpret_cast<v4u*>(dH) + 2 * base + k);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                buf[lane * kBwdStride + r] = v4f{out[4 * r], out[4 * r + 1], out[4 * r + 2], out[4 * r + 3]};
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int k = 64 * q + lane;
+                const v4f o = buf[16 * q * kBwdStride + cpos];
+                if (k < 4 * n) __builtin_nontemporal_store(o, reinterpret_cast<v4f*>(dH) + 4 * base + k);
+            }
         }
         __builtin_amdgcn_wave_barrier();
     }
@@ -1028,9 +1054,6 @@ struct MixChunk {  // channels in one 16-byte chunk of a row
     static constexpr int E = (DX == BIRKHOFF4_BF16) ? 8 : 4;
 };
 
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
 template <int DX>
 __device__ __forceinline__ void unpack_chunk(const v4u w, float v[MixChunk<DX>::E]) {
     const uint32_t u[4] = {w.x, w.y, w.z, w.w};
@@ -1052,7 +1075,7 @@ __device__ __forceinline__ v4u pack_chunk(const float v[MixChunk<DX>::E]) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         if constexpr (DX == BIRKHOFF4_BF16)
-            u[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{v[2 * k], v[2 * k + 1]}), bf16x2));
+            u[k] = pack_bf16(v[2 * k], v[2 * k + 1]);
         else
             u[k] = __float_as_uint(v[k]);
     }
@@ -1093,7 +1116,7 @@ __device__ __forceinline__ void mix_chunk(const float m[N * N], const v4u in[N],
                 for (int j = 1; j < N; ++j) y[e] = __builtin_fmaf(m[TRANS ? N * j + i : N * i + j], x[j][e], y[e]);
             }
             if constexpr (DX == BIRKHOFF4_BF16)
-                o[i][w] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{y[0], y[1]}), bf16x2));
+                o[i][w] = pack_bf16(y[0], y[1]);
             else
                 o[i][w] = __float_as_uint(y[0]);
         }
@@ -2289,10 +2312,12 @@ constexpr int kB8Stride = 17;  // v4f per problem in the LDS tile
 template <bool IN_PLACE, typename T>
 using MaybeRestrict = std::conditional_t<IN_PLACE, T*, T* __restrict__>;
 
-template <int DT, bool OT, bool IN_PLACE = false>
+// DO: dH stored as fp32 or, rounded to nearest even, as bf16 (as in the 4 x 4 backward; 10^6
+// problems, fp32 dP: forward + backward + conversion 366 us, forward + backward 291 us).
+template <int DT, int DO, bool OT, bool IN_PLACE = false>
 __global__ __launch_bounds__(kB8Block, 2) void implicit8_bwd_kernel(const float* __restrict__ P,
                                                                      MaybeRestrict<IN_PLACE, const void> dP,
-                                                                     MaybeRestrict<IN_PLACE, float> dH, int64_t B,
+                                                                     MaybeRestrict<IN_PLACE, void> dH, int64_t B,
                                                                      const float* __restrict__ av, float eta) {
     __shared__ v4f tile_all[kB8Waves][64 * kB8Stride];
     const int lane = threadIdx.x & 63;
@@ -2301,8 +2326,9 @@ __global__ __launch_bounds__(kB8Block, 2) void implicit8_bwd_kernel(const float*
     v4u* const tileu = reinterpret_cast<v4u*>(tile);
     const v4f* P4 = reinterpret_cast<const v4f*>(P);
     const v4u* G4 = reinterpret_cast<const v4u*>(dP);
-    v4f* dH4 = reinterpret_cast<v4f*>(dH);
+    static_assert(!(OT && DO == BIRKHOFF4_BF16) && !(IN_PLACE && DO == BIRKHOFF4_BF16), "bf16 dH: projection only");
     constexpr int GP = (DT == BIRKHOFF4_BF16) ? 8 : 16;  // 16-byte pieces of dP per problem
+    constexpr int HP = (DO == BIRKHOFF4_BF16) ? 8 : 16;  // 16-byte pieces of dH per problem
     const int64_t nchunk = (B + 63) / 64;
     for (int64_t c = static_cast<int64_t>(blockIdx.x) * kB8Waves + wv; c < nchunk;
          c += static_cast<int64_t>(gridDim.x) * kB8Waves) {
@@ -2410,10 +2436,12 @@ __global__ __launch_bounds__(kB8Block, 2) void implicit8_bwd_kernel(const float*
             for (int k = p + 1; k < 8; ++k) s += __builtin_fmaf(W[pw8(p, k)], w[k], F[pw8(p, k)]);
             w[p] = s * ip[p];
         }
-        // dH row i replaces tile slots 2i, 2i+1 of this lane's problem; going down from the
-        // last row, those slots hold only dP rows already read (bf16 rows are 16 bytes)
+        // dH row i replaces tile slots 2i, 2i+1 (bf16: slot i) of this lane's problem. fp32 rows
+        // go down from the last, bf16 rows up from the first: those slots then hold only dP
+        // rows already read, whether a dP row is 16 or 32 bytes
 #pragma unroll
-        for (int i = 7; i >= 0; --i) {
+        for (int ii = 0; ii < 8; ++ii) {
+            const int i = DO == BIRKHOFF4_BF16 ? ii : 7 - ii;
             float G[8], psi[8];
             grow(i, G);
             float mu = 0.f;
@@ -2432,15 +2460,20 @@ __global__ __launch_bounds__(kB8Block, 2) void implicit8_bwd_kernel(const float*
 #pragma unroll
                 for (int j = 0; j < 8; ++j) o[j] = T[8 * i + j] * (psi[j] - mu);
             }
-            tile[lane * kB8Stride + 2 * i] = v4f{o[0], o[1], o[2], o[3]};
-            tile[lane * kB8Stride + 2 * i + 1] = v4f{o[4], o[5], o[6], o[7]};
+            if constexpr (DO == BIRKHOFF4_BF16) {
+                tileu[lane * kB8Stride + i] = v4u{pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]), pack_bf16(o[4], o[5]),
+                                                  pack_bf16(o[6], o[7])};
+            } else {
+                tile[lane * kB8Stride + 2 * i] = v4f{o[0], o[1], o[2], o[3]};
+                tile[lane * kB8Stride + 2 * i + 1] = v4f{o[4], o[5], o[6], o[7]};
+            }
         }
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
+        for (int q = 0; q < HP; ++q) {
             const int k = 64 * q + lane;
-            const v4f o = tile[(k >> 4) * kB8Stride + (k & 15)];
-            if (k < 16 * n) __builtin_nontemporal_store(o, dH4 + 16 * base + k);
+            const v4u o = tileu[(k / HP) * kB8Stride + (k % HP)];
+            if (k < HP * n) __builtin_nontemporal_store(o, reinterpret_cast<v4u*>(dH) + HP * base + k);
         }
         __builtin_amdgcn_wave_barrier();
     }
@@ -3099,6 +3132,29 @@ int64_t grid_for(int64_t B, int block, int cus, int per_cu) {
     return blocks < cap ? blocks : cap;
 }
 
+// The backward kernels take one 64-problem chunk per wave; batches beyond kMaxGrid blocks loop.
+int64_t bwd_grid(int64_t B, int waves) {
+    const int64_t chunks = (B + 63) / 64;
+    const int64_t want = (chunks + waves - 1) / waves;
+    return want < kMaxGrid ? want : kMaxGrid;
+}
+
+template <typename Kernel>
+int launch_bwd(Kernel kern, const float* P, const void* dP, void* dH, int64_t B, hipStream_t stream,
+               const float* hess) {
+    launch_kernel(kern, dim3(static_cast<unsigned>(bwd_grid(B, kBwdWaves))), dim3(kBwdBlock), 0, stream, P, dP, dH, B,
+                  hess);
+    return launch_status();
+}
+
+template <typename Kernel>
+int launch_bwd8(Kernel kern, const float* P, const void* dP, void* dH, int64_t B, hipStream_t stream,
+                const float* a = nullptr, float eta = 1.f) {
+    launch_kernel(kern, dim3(static_cast<unsigned>(bwd_grid(B, kB8Waves))), dim3(kB8Block), 0, stream, P, dP, dH, B, a,
+                  eta);
+    return launch_status();
+}
+
 // Residual mixing, grid-stride over the tokens: one token per wave at a time for n = 4, and
 // for n = 8 one token per block of kMix8Wpt waves once every row has at least one chunk per
 // wave, nc >= 64 kMix8Wpt, which the backward's per-token barrier needs. Both layouts size
@@ -3281,12 +3337,7 @@ int birkhoff8_ot_bwd(const float* T, const float* a, const float* dT, float eta,
     if (misaligned(T) || misaligned(a) || misaligned(dT) || misaligned(dM)) return BIRKHOFF4_ERR_ALIGN;
     const size_t nm = static_cast<size_t>(B) * 256, nv = static_cast<size_t>(B) * 32;
     if (overlaps(dM, nm, T, nm) || overlaps(dM, nm, dT, nm) || overlaps(dM, nm, a, nv)) return BIRKHOFF4_ERR_OVERLAP;
-    const int64_t chunks = (B + 63) / 64;
-    const int64_t want = (chunks + kB8Waves - 1) / kB8Waves;
-    const int64_t grid = want < kMaxGrid ? want : kMaxGrid;
-    launch_kernel((implicit8_bwd_kernel<BIRKHOFF4_F32, true>), dim3(static_cast<unsigned>(grid)),
-                       dim3(kB8Block), 0, stream, T, dT, dM, B, a, eta);
-    return launch_status();
+    return launch_bwd8(implicit8_bwd_kernel<BIRKHOFF4_F32, BIRKHOFF4_F32, true>, T, dT, dM, B, stream, a, eta);
 }
 
 int birkhoff8_fwd(const void* H, int h_dtype, float* P, float* dual, int32_t* iters, int64_t B, float tol,
@@ -3308,46 +3359,45 @@ int birkhoff8_fwd(const void* H, int h_dtype, float* P, float* dual, int32_t* it
     return dispatch_fwd8<BIRKHOFF4_F32>(H, P, dual, iters, B, tol, max_iter, stream);
 }
 
-int birkhoff8_bwd(const float* P, const void* dP, int dp_dtype, float* dH, int64_t B, hipStream_t stream) {
+int birkhoff8_bwd_ex(const float* P, const void* dP, int dp_dtype, void* dH, int dh_dtype, int64_t B,
+                     hipStream_t stream) {
     if (B < 0 || B > (INT64_MAX / 256)) return BIRKHOFF4_ERR_SIZE;
-    if (!dtype_ok(dp_dtype)) return BIRKHOFF4_ERR_DTYPE;
+    if (!dtype_ok(dp_dtype) || !dtype_ok(dh_dtype)) return BIRKHOFF4_ERR_DTYPE;
     if (B == 0) return BIRKHOFF4_OK;
     if (!P || !dP || !dH) return BIRKHOFF4_ERR_NULL;
     if (misaligned(P) || misaligned(dP) || misaligned(dH)) return BIRKHOFF4_ERR_ALIGN;
-    const size_t n = static_cast<size_t>(B) * 256, ng = static_cast<size_t>(B) * 64 * dtype_bytes(dp_dtype);
-    if (overlaps(dH, n, P, n) || overlaps(dH, n, dP, ng)) return BIRKHOFF4_ERR_OVERLAP;
-    const int64_t chunks = (B + 63) / 64;
-    const int64_t want = (chunks + kB8Waves - 1) / kB8Waves;
-    const int64_t grid = want < kMaxGrid ? want : kMaxGrid;
-    if (dp_dtype == BIRKHOFF4_BF16)
-        launch_kernel((implicit8_bwd_kernel<BIRKHOFF4_BF16, false>), dim3(static_cast<unsigned>(grid)),
-                           dim3(kB8Block), 0, stream, P, dP, dH, B, nullptr, 1.f);
-    else
-        launch_kernel((implicit8_bwd_kernel<BIRKHOFF4_F32, false>), dim3(static_cast<unsigned>(grid)),
-                           dim3(kB8Block), 0, stream, P, dP, dH, B, nullptr, 1.f);
-    return launch_status();
+    const size_t n = static_cast<size_t>(B) * 256, ng = static_cast<size_t>(B) * 64 * dtype_bytes(dp_dtype),
+                 nh = static_cast<size_t>(B) * 64 * dtype_bytes(dh_dtype);
+    if (overlaps(dH, nh, P, n) || overlaps(dH, nh, dP, ng)) return BIRKHOFF4_ERR_OVERLAP;
+    constexpr int F = BIRKHOFF4_F32, H = BIRKHOFF4_BF16;
+    auto kern = dp_dtype == H ? (dh_dtype == H ? implicit8_bwd_kernel<H, H, false> : implicit8_bwd_kernel<H, F, false>)
+                              : (dh_dtype == H ? implicit8_bwd_kernel<F, H, false> : implicit8_bwd_kernel<F, F, false>);
+    return launch_bwd8(kern, P, dP, dH, B, stream);
+}
+
+int birkhoff8_bwd(const float* P, const void* dP, int dp_dtype, float* dH, int64_t B, hipStream_t stream) {
+    return birkhoff8_bwd_ex(P, dP, dp_dtype, dH, BIRKHOFF4_F32, B, stream);
+}
+
+int birkhoff4_bwd_ex2(const float* P, const void* dP, int dp_dtype, void* dH, int dh_dtype, int64_t B,
+                      hipStream_t stream) {
+    if (B < 0 || B > (INT64_MAX / 64)) return BIRKHOFF4_ERR_SIZE;
+    if (!dtype_ok(dp_dtype) || !dtype_ok(dh_dtype)) return BIRKHOFF4_ERR_DTYPE;
+    if (B == 0) return BIRKHOFF4_OK;
+    if (!P || !dP || !dH) return BIRKHOFF4_ERR_NULL;
+    if (misaligned(P) || misaligned(dP) || misaligned(dH)) return BIRKHOFF4_ERR_ALIGN;
+    const size_t n = static_cast<size_t>(B) * 64, ng = static_cast<size_t>(B) * 16 * dtype_bytes(dp_dtype),
+                 nh = static_cast<size_t>(B) * 16 * dtype_bytes(dh_dtype);
+    if (overlaps(dH, nh, P, n) || overlaps(dH, nh, dP, ng)) return BIRKHOFF4_ERR_OVERLAP;
+    constexpr int F = BIRKHOFF4_F32, H = BIRKHOFF4_BF16;
+    auto kern = dp_dtype == H ? (dh_dtype == H ? implicit_bwd_kernel<H, H> : implicit_bwd_kernel<H, F>)
+                              : (dh_dtype == H ? implicit_bwd_kernel<F, H> : implicit_bwd_kernel<F, F>);
+    return launch_bwd(kern, P, dP, dH, B, stream, nullptr);
 }
 
 int birkhoff4_bwd_ex(const float* P, const void* dP, int dp_dtype, float* dH, int64_t B,
                      hipStream_t stream) {
-    if (B < 0 || B > (INT64_MAX / 64)) return BIRKHOFF4_ERR_SIZE;
-    if (!dtype_ok(dp_dtype)) return BIRKHOFF4_ERR_DTYPE;
-    if (B == 0) return BIRKHOFF4_OK;
-    if (!P || !dP || !dH) return BIRKHOFF4_ERR_NULL;
-    if (misaligned(P) || misaligned(dP) || misaligned(dH)) return BIRKHOFF4_ERR_ALIGN;
-    const size_t n = static_cast<size_t>(B) * 64, ng = static_cast<size_t>(B) * 16 * dtype_bytes(dp_dtype);
-    if (overlaps(dH, n, P, n) || overlaps(dH, n, dP, ng)) return BIRKHOFF4_ERR_OVERLAP;
-    // One 64-problem chunk per wave; batches beyond kMaxGrid blocks loop.
-    const int64_t chunks = (B + 63) / 64;
-    const int64_t want = (chunks + kBwdWaves - 1) / kBwdWaves;
-    const int64_t grid = want < kMaxGrid ? want : kMaxGrid;
-    if (dp_dtype == BIRKHOFF4_BF16)
-        launch_kernel(implicit_bwd_kernel<BIRKHOFF4_BF16>, dim3(static_cast<unsigned>(grid)), dim3(kBwdBlock),
-                           0, stream, P, dP, dH, B, nullptr);
-    else
-        launch_kernel(implicit_bwd_kernel<BIRKHOFF4_F32>, dim3(static_cast<unsigned>(grid)), dim3(kBwdBlock),
-                           0, stream, P, dP, dH, B, nullptr);
-    return launch_status();
+    return birkhoff4_bwd_ex2(P, dP, dp_dtype, dH, BIRKHOFF4_F32, B, stream);
 }
 
 int birkhoff4_bwd_hess(const float* P, const float* hess, const void* dP, int dp_dtype, float* dH, int64_t B,
@@ -3360,16 +3410,9 @@ int birkhoff4_bwd_hess(const float* P, const float* hess, const void* dP, int dp
     const size_t n = static_cast<size_t>(B) * 64, ng = static_cast<size_t>(B) * 16 * dtype_bytes(dp_dtype),
                  nw = static_cast<size_t>(B) * 32;
     if (overlaps(dH, n, P, n) || overlaps(dH, n, dP, ng) || overlaps(dH, n, hess, nw)) return BIRKHOFF4_ERR_OVERLAP;
-    const int64_t chunks = (B + 63) / 64;
-    const int64_t want = (chunks + kBwdWaves - 1) / kBwdWaves;
-    const int64_t grid = want < kMaxGrid ? want : kMaxGrid;
-    if (dp_dtype == BIRKHOFF4_BF16)
-        launch_kernel((implicit_bwd_kernel<BIRKHOFF4_BF16, true>), dim3(static_cast<unsigned>(grid)),
-                           dim3(kBwdBlock), 0, stream, P, dP, dH, B, hess);
-    else
-        launch_kernel((implicit_bwd_kernel<BIRKHOFF4_F32, true>), dim3(static_cast<unsigned>(grid)),
-                           dim3(kBwdBlock), 0, stream, P, dP, dH, B, hess);
-    return launch_status();
+    constexpr int F = BIRKHOFF4_F32, H = BIRKHOFF4_BF16;
+    auto kern = dp_dtype == H ? implicit_bwd_kernel<H, F, true> : implicit_bwd_kernel<F, F, true>;
+    return launch_bwd(kern, P, dP, dH, B, stream, hess);
 }
 
 int birkhoff4_bwd(const float* P, const float* dual, const float* dP, float* dH, int64_t B,
@@ -3554,12 +3597,7 @@ int birkhoff8_mix_bwd(const float* P, const void* X, const void* dY, int x_dtype
     const int e = x_dtype == BIRKHOFF4_BF16 ? launch_mix_bwd<BIRKHOFF4_BF16, 8>(P, X, dY, dX, dH, B, nc, stream, cus)
                                             : launch_mix_bwd<BIRKHOFF4_F32, 8>(P, X, dY, dX, dH, B, nc, stream, cus);
     if (e) return e;
-    const int64_t chunks = (B + 63) / 64;
-    const int64_t want = (chunks + kB8Waves - 1) / kB8Waves;
-    const int64_t grid = want < kMaxGrid ? want : kMaxGrid;
-    launch_kernel((implicit8_bwd_kernel<BIRKHOFF4_F32, false, true>), dim3(static_cast<unsigned>(grid)),
-                  dim3(kB8Block), 0, stream, P, dH, dH, B, nullptr, 1.f);
-    return launch_status();
+    return launch_bwd8(implicit8_bwd_kernel<BIRKHOFF4_F32, BIRKHOFF4_F32, false, true>, P, dH, dH, B, stream);
 }
 
 const char* birkhoff4_strerror(int code) {
