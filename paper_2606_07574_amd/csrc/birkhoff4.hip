@@ -85,6 +85,18 @@ constexpr int kSkRegSteps = 20;   // step count whose backward keeps the iterate
 constexpr int kMaxIterCap = 10000;
 // Batches up to this size take the four-lanes-per-problem forward by default.
 constexpr int64_t kLatencyMaxB = int64_t(1) << 15;
+// n = 8: the fewest rows per lane whose waves still fit one per SIMD (1024 SIMDs, 8 R problems
+// per wave), up to four rows and then two waves per SIMD; beyond, one problem per lane. Forward
+// times in us, on N(0,1) / the mixture of N(0, s^2) and near-permutations / OT with eta = 0.5:
+//    B      one row            two rows           four rows          one problem per lane
+//    4096    7.1 / 21.0 / 17.3   7.4 / 21.9 / 18.7   8.7 / 27.3 / 22.8  13.7 / 54.8 / 39.6
+//   12288   10.4 / 31.7 / 26.8   8.2 / 22.8 / 21.9  10.1 / 28.1 / 25.8  13.7 / 43.6 / 37.2
+//   24576   14.5 / 40.9 / 33.4  12.2 / 34.0 / 27.4  10.7 / 29.2 / 27.0  14.1 / 39.6 / 37.0
+//   65536   31.3 / 85.8 / 69.8  20.4 / 59.4 / 47.4  17.3 / 43.8 / 37.9  20.3 / 53.2 / 42.9
+//   98304   43.2 / 119  / 97.5  27.1 / 79.0 / 67.3  23.5 / 60.8 / 54.5  24.2 / 56.8 / 46.8
+constexpr int64_t kOneRowMaxB8 = 8192;
+constexpr int64_t kTwoRowMaxB8 = 16384;
+constexpr int64_t kFourRowMaxB8 = 65536;
 constexpr int64_t kMaxGrid = int64_t(1) << 24;  // blocks of a streaming launch
 constexpr int kFwdBlock = 1024;  // one workgroup per CU: 16 waves, 4 per SIMD
 constexpr int kFwdWaves = kFwdBlock / 64;
@@ -2291,6 +2303,285 @@ __global__ __launch_bounds__(kB8Block, 2) void newton8_fwd_kernel(const void* __
     }
 }
 
+// n = 8 forward, latency variant: several lanes per problem, R rows each (8 / R lanes). Up to
+// a few tens of thousands of problems the one-problem-per-lane kernel is bound by the serial
+// chain of one trial (about a thousand instructions of one lane) times the slowest problem's
+// trials, on a chip that is mostly idle. Here the row-wise work and the weight sums of a trial
+// are split over the group (its sums are DPP butterflies, bitwise the same in all of its
+// lanes), and the 7-node solve and the step control run replicated. No refill: a wave holds
+// 8 R problems until the slowest is done, and a block is one wave, so that small batches reach
+// every CU. The iteration is the throughput kernel's. Bound: the dependent chain of a trial
+// (about 1.3 us with one row per lane against 2.7 us for one problem per lane).
+
+// Sum over a group of G lanes, the same value in all of them (contraction off as in qsum):
+// partners (1,0,3,2), then (2,3,0,1), then, with eight lanes, the other quad by a mirror.
+template <int G>
+__device__ __forceinline__ float gsum_lanes(float x) {
+#pragma clang fp contract(off)
+    if constexpr (G == 2) return psum(x);
+    x = qsum(x);
+    if constexpr (G == 8)
+        x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x141, 0xF, 0xF, true));  // row_half_mirror
+    return x;
+}
+
+constexpr int kGrp8Block = 64;
+
+template <int R, int DT, bool WRITE_DUAL, bool WRITE_ITERS, bool OT>
+__global__ __launch_bounds__(kGrp8Block) void newton8_fwd_group_kernel(const void* __restrict__ H,
+                                                                       float* __restrict__ P, float* __restrict__ dual,
+                                                                       int32_t* __restrict__ iters, int64_t B,
+                                                                       float tol, int max_iter,
+                                                                       const float* __restrict__ av,
+                                                                       const float* __restrict__ bv, float eta) {
+    constexpr int G = 8 / R;                        // lanes per problem
+    const float hsc = OT ? -kLog2e / eta : kLog2e;  // log2-unit logits per unit of H (or of M)
+    const int64_t b = static_cast<int64_t>(blockIdx.x) * (kGrp8Block / G) + threadIdx.x / G;  // this group's problem
+    const int q = threadIdx.x % G;  // this lane's rows: R q .. R q + R - 1
+    const bool valid = b < B;       // uniform across the group
+    float h[R][8], ma[R], mb[8];    // logits; OT: these rows' masses and all column masses
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) h[r][j] = 0.f;
+        ma[r] = 1.f;
+        if (valid) {
+            load_row8<DT>(H, b, R * q + r, h[r]);
+            if constexpr (OT) ma[r] = av[8 * b + R * q + r];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) mb[j] = 1.f;
+    bool fin = true;
+    if constexpr (OT) {
+        if (valid) {
+            const v4f b0 = reinterpret_cast<const v4f*>(bv)[2 * b], b1 = reinterpret_cast<const v4f*>(bv)[2 * b + 1];
+            mb[0] = b0.x; mb[1] = b0.y; mb[2] = b0.z; mb[3] = b0.w;
+            mb[4] = b1.x; mb[5] = b1.y; mb[6] = b1.z; mb[7] = b1.w;
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) fin = fin && __builtin_isfinite(ma[r]) && ma[r] > 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) fin = fin && __builtin_isfinite(mb[j]) && mb[j] > 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) fin = fin && __builtin_isfinite(h[r][j]);
+    fin = gsum_lanes<G>(fin ? 0.f : 1.f) == 0.f;  // the whole problem
+    const float poison = fin ? 0.f : __builtin_nanf("");
+    // initial point (column centring), as in the throughput kernel's init_batch
+    float beta[7], T[R][8], a[R];
+    {
+        float cm[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            float c = h[0][j] * hsc;
+#pragma unroll
+            for (int r = 1; r < R; ++r) c += h[r][j] * hsc;
+            cm[j] = gsum_lanes<G>(c);
+        }
+#pragma unroll
+        for (int j = 0; j < 7; ++j) beta[j] = 0.125f * (cm[7] - cm[j]) + poison;
+        if constexpr (OT) {
+            const float ib7 = rcp(mb[7]);
+#pragma unroll
+            for (int j = 0; j < 7; ++j) beta[j] += lg2(mb[j] * ib7);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            float u[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) u[j] = __builtin_fmaf(h[r][j], hsc, j < 7 ? beta[j] : poison);
+            float m = u[0];
+#pragma unroll
+            for (int j = 1; j < 8; ++j) m = __builtin_fmaxf(m, u[j]);
+            m += poison;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) T[r][j] = ex2(u[j] - m);
+            const float sum = sum8(T[r]);
+            const float rc = rcp(sum);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) T[r][j] *= rc;
+            a[r] = m + lg2(sum);
+        }
+    }
+    float sa = 8.f, sb = 8.f;  // total row and column masses
+    if constexpr (OT) {
+        sa = ma[0];
+#pragma unroll
+        for (int r = 1; r < R; ++r) sa += ma[r];
+        sa = gsum_lanes<G>(sa);
+        sb = sum8v(mb);
+    }
+    const float fnoise = OT ? kFNoise * 0.125f * sa : kFNoise, lmfloor = OT ? kLMFloor * 0.125f * sa : kLMFloor;
+    float g[8], W[28], ga[7];
+    // each row's contribution is formed before the sum over the rows and the group
+    auto gradient = [&]() {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            float c = OT ? ma[0] * T[0][j] : T[0][j];
+#pragma unroll
+            for (int r = 1; r < R; ++r) c = OT ? __builtin_fmaf(ma[r], T[r][j], c) : c + T[r][j];
+            g[j] = gsum_lanes<G>(c) - (OT ? mb[j] : 1.f);
+        }
+    };
+    auto weights = [&]() {
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {
+            float w[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) w[r] = OT ? ma[r] * T[r][j] : T[r][j];
+#pragma unroll
+            for (int k = j + 1; k < 8; ++k) {
+                float c = w[0] * T[0][k];
+#pragma unroll
+                for (int r = 1; r < R; ++r) c = __builtin_fmaf(w[r], T[r][k], c);
+                W[pw8(j, k)] = gsum_lanes<G>(c);
+            }
+        }
+    };
+    auto gmax_of = [&]() {
+        float m = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) m = __builtin_fmaxf(m, __builtin_fabsf(g[j]));
+        return m;
+    };
+    auto norm2_of = [&]() {
+        float m = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) m = __builtin_fmaf(g[j], g[j], m);
+        return m;
+    };
+    // move the columns by s: product-form evaluation of this lane's rows (as evaluate8), l the
+    // log2 row sums
+    auto move = [&](const float s[7], float l[R]) {
+        float S[7];
+#pragma unroll
+        for (int j = 0; j < 7; ++j) S[j] = ex2(s[j]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+#pragma unroll
+            for (int j = 0; j < 7; ++j) T[r][j] *= S[j];
+            const float sum = sum8(T[r]);
+            const float rc = rcp(sum);
+            l[r] = lg2(sum);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) T[r][j] *= rc;
+            a[r] += l[r];
+        }
+    };
+    gradient();
+    float gmax = gmax_of();
+    const bool conv0 = OT ? ot_within_tol8(g, mb, tol, sa, sb) : gmax <= tol;
+    bool active = valid && !conv0 && fin && max_iter > 0;
+    int status = !fin ? BIRKHOFF4_NON_FINITE : (conv0 ? 0 : BIRKHOFF4_NOT_CONVERGED);
+    weights();
+#pragma unroll
+    for (int j = 0; j < 7; ++j) ga[j] = g[j];
+    float lam = __builtin_fmaxf(kLM * gmax, lmfloor), gn2 = norm2_of();
+    float t = 1.f, fofs = 0.f, gsum = 0.f, o[7];
+#pragma unroll
+    for (int j = 0; j < 7; ++j) o[j] = 0.f;
+    int cnt = 0;  // bits 0-15: trial steps; bits 16-18: log2 of the initial trial step
+    while (__ballot(active)) {
+        if (active) {
+            float d[7], s[7], l[R];
+            newton_solve8(W, ga, lam, d);
+            t = __builtin_fminf(t, kCap2 * rcp(__builtin_fmaxf(spread8(d), kTiny)));
+#pragma unroll
+            for (int j = 0; j < 7; ++j) s[j] = __builtin_fmaf(t, d[j], -o[j]);
+            move(s, l);
+            gradient();
+            float ls = OT ? ma[0] * l[0] : l[0], ss = 0.f;
+#pragma unroll
+            for (int r = 1; r < R; ++r) ls = OT ? __builtin_fmaf(ma[r], l[r], ls) : ls + l[r];
+#pragma unroll
+            for (int j = 0; j < 7; ++j) {
+                beta[j] += s[j];
+                o[j] += s[j];
+                ss = OT ? __builtin_fmaf(mb[j], s[j], ss) : ss + s[j];
+            }
+            const float df = fofs + (gsum_lanes<G>(ls) - ss);
+            fofs = df;
+            gsum += spread8(s);
+            ++cnt;
+            gmax = gmax_of();
+            const float gn2t = norm2_of();
+            float slope = 0.f;
+#pragma unroll
+            for (int j = 0; j < 7; ++j) slope = __builtin_fmaf(ga[j], d[j], slope);
+            const bool accept = (df <= kArmijo * t * slope) || (__builtin_fabsf(df) < fnoise && gn2t < gn2);
+            const int evals = cnt & 0xffff;
+            const bool conv = accept && (OT ? ot_within_tol8(g, mb, tol, sa, sb) : gmax <= tol);
+            if (!conv && evals < max_iter) {
+                if (gsum >= kReviveBits) {  // flushed entries: re-derive from H (per lane)
+                    gsum = 0.f;
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                        for (int j = 0; j < 8; ++j)
+                            if (T[r][j] == 0.f)
+                                T[r][j] = ex2(__builtin_fmaf(h[r][j], hsc, j < 7 ? beta[j] : 0.f) - a[r]);
+                }
+                if (accept) {
+                    float dd = 0.f;
+#pragma unroll
+                    for (int j = 0; j < 7; ++j) dd = __builtin_fmaf(g[j], d[j], dd);
+                    const int ts = cnt >> 16;
+                    const bool grow = t >= 0.999f * __builtin_ldexpf(1.f, ts) && dd < 0.25f * slope;
+                    cnt = evals | ((grow ? (ts < kMaxExpandLog2 ? ts + 1 : ts) : 0) << 16);
+                    fofs = 0.f;
+                    gn2 = gn2t;
+                    weights();
+#pragma unroll
+                    for (int j = 0; j < 7; ++j) {
+                        o[j] = 0.f;
+                        ga[j] = g[j];
+                    }
+                    lam = __builtin_fmaxf(kLM * gmax, lmfloor);
+                    t = __builtin_ldexpf(1.f, cnt >> 16);
+                } else {
+                    t *= 0.5f;
+                    cnt = evals;
+                    lam = __builtin_fminf(16.f * lam, kMaxShift);
+                }
+            } else {
+                if (!accept) {  // max_iter reached on a rejected trial: back to the accepted point
+                    float back[7];
+#pragma unroll
+                    for (int j = 0; j < 7; ++j) {
+                        back[j] = -o[j];
+                        beta[j] -= o[j];
+                    }
+                    move(back, l);
+                }
+                status = conv ? evals : BIRKHOFF4_NOT_CONVERGED;
+                active = false;
+            }
+        }
+    }
+    if (!valid) return;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = R * q + r;
+        v4f* pp = reinterpret_cast<v4f*>(P) + 16 * b + 2 * i;
+        const float m = OT ? ma[r] : 1.f;
+        pp[0] = v4f{m * T[r][0], m * T[r][1], m * T[r][2], m * T[r][3]};
+        pp[1] = v4f{m * T[r][4], m * T[r][5], m * T[r][6], m * T[r][7]};
+        if constexpr (WRITE_DUAL) {
+            float x = beta[0] * 0.f;  // beta_8 = 0, NaN if poisoned
+#pragma unroll
+            for (int j = 0; j < 7; ++j) x = i == j ? beta[j] : x;
+            const float e2 = OT ? eta * kLn2 : kLn2;
+            dual[16 * b + i] = OT ? e2 * (lg2(m) - a[r]) : -a[r] * e2;
+            dual[16 * b + 8 + i] = i < 7 ? x * e2 : x;
+        }
+    }
+    if constexpr (WRITE_ITERS)
+        if (q == 0) iters[b] = status;
+}
+
 // Backward for n = 8 (eq. derivative, a = b = 1, eta = 1), the flow form of the 4 x 4
 // kernel: W_jk = sum_i T_ij T_ik and antisymmetric flows F_jk = sum_i T_ij T_ik
 // (G_ij - G_ik); eliminating node p adds W_jp W_pk / piv to edge (j, k) and
@@ -3073,10 +3364,24 @@ int fwd8_blocks_per_cu(int dev) {
     return cached[dev];
 }
 
+// n = 8, latency variant: one wave per block, 8 R problems each.
+template <int R, int DT, bool WD, bool WI, bool OT>
+int launch_fwd8_group(const void* H, float* P, float* dual, int32_t* iters, int64_t B, float tol, int max_iter,
+                      hipStream_t stream, const float* a, const float* b, float eta) {
+    constexpr int kProblems = kGrp8Block / (8 / R);
+    launch_kernel((newton8_fwd_group_kernel<R, DT, WD, WI, OT>),
+                  dim3(static_cast<unsigned>((B + kProblems - 1) / kProblems)), dim3(kGrp8Block), 0, stream, H, P, dual,
+                  iters, B, tol, max_iter, a, b, eta);
+    return launch_status();
+}
+
 // n = 8: the grid is the resident waves (fewer for small B), each taking every nwv-th batch.
 template <int DT, bool WD, bool WI, bool OT = false>
 int launch_fwd8(const void* H, float* P, float* dual, int32_t* iters, int64_t B, float tol, int max_iter,
                 hipStream_t stream, const float* a = nullptr, const float* b = nullptr, float eta = 1.f) {
+    if (B <= kOneRowMaxB8) return launch_fwd8_group<1, DT, WD, WI, OT>(H, P, dual, iters, B, tol, max_iter, stream, a, b, eta);
+    if (B <= kTwoRowMaxB8) return launch_fwd8_group<2, DT, WD, WI, OT>(H, P, dual, iters, B, tol, max_iter, stream, a, b, eta);
+    if (B <= kFourRowMaxB8) return launch_fwd8_group<4, DT, WD, WI, OT>(H, P, dual, iters, B, tol, max_iter, stream, a, b, eta);
     int cus = 0, dev = 0;
     if (int e = device_cus(stream, &cus, &dev)) return e;
     const int64_t batches = (B + kB8Ring - 1) / kB8Ring;
