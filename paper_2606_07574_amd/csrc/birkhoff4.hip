@@ -685,6 +685,25 @@ __device__ __forceinline__ float qsum(float x) {
     return x;
 }
 
+// Sum over the two lanes of a pair (2k, 2k + 1); both receive the same value (the add
+// commutes, and contraction is off so that it is not fused into the caller's product).
+__device__ __forceinline__ float psum(float x) {
+#pragma clang fp contract(off)
+    return x + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, true));
+}
+
+// Sum over a group of G lanes, the same value in all of them (contraction off as in qsum):
+// partners (1,0,3,2), then (2,3,0,1), then, with eight lanes, the other quad by a mirror.
+template <int G>
+__device__ __forceinline__ float gsum_lanes(float x) {
+#pragma clang fp contract(off)
+    if constexpr (G == 2) return psum(x);
+    x = qsum(x);
+    if constexpr (G == 8)
+        x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x141, 0xF, 0xF, true));  // row_half_mirror
+    return x;
+}
+
 // The value held by lane k of the quad, in every lane of the quad.
 template <int K>
 __device__ __forceinline__ float qget(float x) {
@@ -1053,14 +1072,10 @@ __global__ __launch_bounds__(kBwdBlock) void implicit_bwd_kernel(const float* __
 // A token carries n = 4 (or 8) streams of C channels, [B][n][C] row-major. The forward
 // writes Y_i = sum_j P_ij X_j; the backward writes dX_j = sum_i P_ij dY_i and forms
 // dP_ij = sum_c dY_i[c] X_j[c], from which dH follows as in the projection's backward. A
-// wave works on one token at a time (with n = 8, the four waves of a block on the same
-// token): P is uniform over the wave (scalar loads) and the lanes stream 16-byte chunks of
-// the rows, so that each load or store instruction covers 1 KB of one row. Every stream
-// byte is touched once: non-temporal loads and stores.
-constexpr int kMixBlock = 256;
-constexpr int kMixWaves = kMixBlock / 64;
-constexpr int kMixPerCu = 8;  // blocks per CU the grid is sized for
-
+// block works on one token (or, where a row is short, each of its waves on one): P is uniform
+// over the wave (scalar loads) and the lanes take 16-byte chunks of the rows, so that each
+// load or store instruction covers 1 KB of one row. Every stream byte is touched once:
+// non-temporal loads and stores.
 template <int DX>
 struct MixChunk {  // channels in one 16-byte chunk of a row
     static constexpr int E = (DX == BIRKHOFF4_BF16) ? 8 : 4;
@@ -1145,306 +1160,313 @@ __device__ __forceinline__ void load_token_matrix(const float* __restrict__ P, i
     for (int q = 0; q < N * N; ++q) p[q] = pt[q];
 }
 
-// A wave walks the items (t, c0) of its tokens: lane l handles chunk c0 + l of each of the
-// N rows. With one wave per token (WPT = 1) c0 = 0, 64, 128, ... < nc; with WPT waves per
-// token, wave s of the token takes c0 = 64 s, 64 (s + WPT), ..., so that the token's waves
-// stream adjacent kilobytes of each row together. (Eight rows per token are sixteen or
-// twenty-four separate streams per wave; measured on a plain copy of this pattern, HBM
-// delivers about 10% more when four waves share a token's rows than when one wave walks
-// them alone. In the 8-stream backward two or eight waves per token measured 5-8% slower
-// than four. Four rows stream best one token per wave.) The next item's loads are issued
-// before the current item is mixed and stored (loads and stores retire in order, so a
-// wait for loads issued after a store would also wait for that store), into the other of
-// two buffers so that no register copy waits for them. Lanes past the end of a row take
-// its last chunk: they load, mix and store the same bytes as that chunk's own lane, so
-// every memory instruction is issued by the whole wave and the waits count exactly.
-// A block of kMixWaves waves takes kMixWaves tokens at a time (WPT = 1); with WPT > 1 the
-// block is the WPT waves of one token.
-constexpr int kMix8Wpt = 4;  // waves per token of the n = 8 kernels
-
-template <int WPT>
-struct MixWalk {  // a wave's first token and chunk, and the strides of its walk
-    static constexpr int kTokensPerBlock = WPT == 1 ? kMixWaves : 1;
-    static constexpr int kBlockThreads = WPT == 1 ? kMixBlock : 64 * WPT;
-    static constexpr int64_t kStep = 64 * WPT;
-    static __device__ __forceinline__ int wave() {
-        return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
-    }
-    static __device__ __forceinline__ int64_t first_token() {
-        return static_cast<int64_t>(blockIdx.x) * kTokensPerBlock + (WPT == 1 ? wave() : 0);
-    }
-    static __device__ __forceinline__ int64_t first_chunk() { return 64 * (wave() % WPT); }
-    static __device__ __forceinline__ int64_t token_stride() {
-        return static_cast<int64_t>(gridDim.x) * kTokensPerBlock;
-    }
-};
-
-template <int DX, int N, int WPT = 1>
-__global__ __launch_bounds__(kMixBlock) void mix_fwd_kernel(const float* __restrict__ P,
-                                                             const v4u* __restrict__ X, v4u* __restrict__ Y,
-                                                             int64_t B, int64_t nc) {
-    using W = MixWalk<WPT>;
-    const int lane = threadIdx.x & 63;
-    const int64_t stride = W::token_stride();
-    const int64_t cfirst = W::first_chunk();
-    int64_t t = W::first_token();
-    if (t >= B || cfirst >= nc) return;  // uniform over the wave; nc >= 1 here
-    int64_t c0 = cfirst;
-    auto offset = [&](int64_t tt, int64_t cc0) {
-        const int64_t cc = cc0 + lane;
-        return N * nc * tt + (cc < nc ? cc : nc - 1);
-    };
-    auto load_item = [&](int64_t off, v4u v[N]) {
-#pragma unroll
-        for (int j = 0; j < N; ++j) v[j] = __builtin_nontemporal_load(X + off + j * nc);
-    };
-    float p[N * N];
-    load_token_matrix<N>(P, t, p);
-    // mix the item in `cur` while the next one (or, after the last, this one again) loads
-    // into `nxt`
-    auto step = [&](const v4u cur[N], v4u nxt[N]) {
-        int64_t tn = t, cn = c0 + W::kStep;
-        if (cn >= nc) {
-            cn = cfirst;
-            tn = t + stride;
-        }
-        const bool more = tn < B;
-        load_item(more ? offset(tn, cn) : offset(t, c0), nxt);
-        __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of the waits for `cur`
-        v4u out[N];
-        mix_chunk<DX, N>(p, cur, out);
-        const int64_t off = offset(t, c0);
-#pragma unroll
-        for (int i = 0; i < N; ++i) __builtin_nontemporal_store(out[i], Y + off + i * nc);
-        if (more && tn != t) load_token_matrix<N>(P, tn, p);
-        t = tn;
-        c0 = cn;
-    };
-    // The first step is peeled and the rest run as a counted loop of two steps: each step's
-    // loads are then used unconditionally by the next one (so they stay where they are
-    // issued), and every path into a step leaves the same loads and stores in flight (so the
-    // wait for `cur` does not cover the previous step's stores).
-    const int64_t items = ((B - t + stride - 1) / stride) * ((nc - cfirst + W::kStep - 1) / W::kStep);
-    v4u a[N], b[N];
-    load_item(offset(t, cfirst), a);
-    step(a, b);
-    int64_t k = 1;
-    for (; k + 2 <= items; k += 2) {
-        step(b, a);
-        step(a, b);
-    }
-    if (k < items) step(b, a);
+// Tokens of the grid's blocks. Workgroups go to the eight XCDs in turn; here each XCD gets
+// windows of `win` consecutive tokens, so that the rows one L2 streams lie together. Tokens
+// past the last whole set of windows keep their order.
+__device__ __forceinline__ int64_t mix_token(int64_t k, int64_t count, int win) {
+    const int64_t set = 8 * static_cast<int64_t>(win);
+    const int64_t base = k / set * set;
+    if (base + set > count) return k;
+    const int r = static_cast<int>(k - base);
+    return base + static_cast<int64_t>(r & 7) * win + (r >> 3);
 }
 
-// Sum over the 64 lanes of the wave of each of v[0..15]; every lane receives all sixteen
-// sums. Halving exchange: at lane mask m a lane keeps the half of its values selected by
-// its bit m and adds its partner's copy of that half, so after masks 32, 16, 8, 4 lane L
-// holds value (L >> 2) & 15 summed over the lanes that share its two low bits; two more
-// exchanges complete the sums (17 shuffles instead of 96).
-// The same exchange for 64 values: after masks 32 .. 1 lane L holds the wave's sum of
-// value L (63 shuffles). Each step writes a new array of half the size, so that every value
-// stays in a register.
+// A row of nc chunks is ceil(nc / 64) columns of 64. Block (64 W, T): T tokens of W waves
+// each, a column per wave, lanes past the end of the row idle. A wave loads its column of
+// every row, mixes, stores and ends (a row of more columns than the launch has waves makes it
+// go round): HBM streams better from many short waves than from a resident grid whose waves
+// walk the tokens and prefetch the next item. Bound: HBM. At 4 x 4096 bf16 channels, 2^15
+// tokens, resident grid -> this: forward 373 -> 344 us (6.2 TB/s), backward 556 -> 517 us
+// (6.2 TB/s); 8 x 4096, 2^14 tokens: forward 387 -> 337 us, backward 577 -> 514 us; 3 * 10^4
+// tokens of 4 x 1000: 100 -> 84 us and 159 -> 115 us. Two columns per wave measured slower
+// (4 x 1000: 93 and 127 us) or the same.
+constexpr int kMixMaxWaves = 16;
+
+template <int DX, int N>
+__global__ __launch_bounds__(64 * kMixMaxWaves) void mix_fwd_kernel(const float* __restrict__ P,
+                                                                    const v4u* __restrict__ X, v4u* __restrict__ Y,
+                                                                    int64_t B, int64_t nc, int win) {
+    const unsigned lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int ty = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.y));
+    const int W = blockDim.x >> 6;
+    const int64_t count = (B + blockDim.y - 1) / blockDim.y;  // groups of T tokens
+    for (int64_t k = blockIdx.x; k < count; k += gridDim.x) {
+        const int64_t t = mix_token(k, count, win) * blockDim.y + ty;
+        if (t >= B) continue;  // uniform over the wave
+        // blockIdx.y: which share of the row
+        for (int64_t col = 64 * (static_cast<int64_t>(blockIdx.y) * W + w); col < nc;
+             col += 64 * static_cast<int64_t>(gridDim.y) * W) {
+            const int64_t off = N * nc * t + col;  // uniform: scalar row addresses, the lane a 32-bit offset
+            const bool own = lane < nc - col;
+            v4u x[N], y[N];
+            if (own) {
+#pragma unroll
+                for (int j = 0; j < N; ++j) x[j] = __builtin_nontemporal_load(X + (off + j * nc) + lane);
+            }
+            float p[N * N];
+            load_token_matrix<N>(P, t, p);
+            if (own) {
+                mix_chunk<DX, N>(p, x, y);
+#pragma unroll
+                for (int j = 0; j < N; ++j) __builtin_nontemporal_store(y[j], Y + (off + j * nc) + lane);
+            }
+        }
+    }
+}
+
+// Sums over lanes by halving exchanges: a step adds, for each pair of values, the two halves
+// of the lanes that differ in bit M, and leaves one value of the pair in each half, so 2 n
+// values become n. Between the halves of the wave and of 32 lanes that is a register swap and
+// an add; within 16 lanes a DPP move (half-mirror for the partner across 4: lanes i and 7 - i,
+// whose lower bits the later steps sum over).
 template <int M>
-__device__ __forceinline__ void halve_step(const float (&v)[2 * M], float (&h)[M], int lane) {
-    const bool hi = (lane & M) != 0;
-#pragma unroll
-    for (int k = 0; k < M; ++k) {
-        const float send = hi ? v[k] : v[k + M];
-        const float keep = hi ? v[k + M] : v[k];
-        h[k] = keep + __shfl_xor(send, M);
+__device__ __forceinline__ float halve_pair(float a, float b, int lane) {
+    if constexpr (M == 32 || M == 16) {
+        const auto r = M == 32 ? __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false)
+                               : __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    } else {
+        constexpr int kCtrl = M == 8 ? 0x128 : M == 4 ? 0x141 : M == 2 ? 0x4E : 0xB1;  // row_ror:8, half-mirror, quad_perm
+        const bool hi = (lane & M) != 0;
+        const float keep = hi ? b : a, send = hi ? a : b;
+        return keep + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(send), kCtrl, 0xF, 0xF, true));
     }
 }
 
-__device__ __forceinline__ float wave_sum64_own(const float (&v)[64], int lane) {
-    float a[32], b[16], c[8], d[4], e[2], f[1];
-    halve_step<32>(v, a, lane);
-    halve_step<16>(a, b, lane);
-    halve_step<8>(b, c, lane);
-    halve_step<4>(c, d, lane);
-    halve_step<2>(d, e, lane);
-    halve_step<1>(e, f, lane);
-    return f[0];
-}
-
-__device__ __forceinline__ void wave_sum16(float v[16], int lane, float s[16]) {
+// The values v[0 .. NV) summed over the 2 M lanes that share the bits above M: lane c of them
+// keeps the sums of values NV / (2 M) c onwards (NV / (2 M) of them), or, where NV < 2 M, the
+// one of value c NV / (2 M), its lowest bits still to be summed over.
+template <int M, int NV>
+__device__ __forceinline__ void lane_sums(const float (&v)[NV], float (&out)[NV / (2 * M) > 0 ? NV / (2 * M) : 1],
+                                          int lane) {
+    if constexpr (M == 0 || NV == 1) {
 #pragma unroll
-    for (int step = 0; step < 4; ++step) {
-        const int m = 32 >> step, n = 8 >> step;
-        const bool hi = (lane & m) != 0;
+        for (int k = 0; k < NV; ++k) out[k] = v[k];
+    } else {
+        float h[NV / 2];
 #pragma unroll
-        for (int k = 0; k < n; ++k) {
-            const float send = hi ? v[k] : v[k + n];
-            const float keep = hi ? v[k + n] : v[k];
-            v[k] = keep + __shfl_xor(send, m);
-        }
-    }
-    float r = v[0];
-    r += __shfl_xor(r, 1);
-    r += __shfl_xor(r, 2);
+        for (int k = 0; k < NV / 2; ++k) h[k] = halve_pair<M>(v[k], v[k + NV / 2], lane);
+        if constexpr (M == 1) {
 #pragma unroll
-    for (int q = 0; q < 16; ++q) s[q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r), 4 * q));
-}
-
-// The same walk; a token's dP is summed over the wave when its last item is done, while
-// the next item's loads are in flight. Lanes past the end of a row zero their X words, so
-// that the chunk they repeat adds nothing to dP. With several waves per token (n = 8 only,
-// all the block's waves on one token at a time) each wave leaves its sums in LDS and the
-// block's first wave adds them in wave order, so the result does not depend on timing.
-// That takes a barrier per token, which every wave must reach equally often: each wave
-// needs at least one item per token, nc >= 64 WPT (the launcher's condition).
-template <int DX, int N, int WPT = 1>
-__global__ __launch_bounds__(kMixBlock) void mix_bwd_kernel(const float* __restrict__ P,
-                                                             const v4u* __restrict__ X,
-                                                             const v4u* __restrict__ dY, v4u* __restrict__ dX,
-                                                             float* __restrict__ dH, int64_t B, int64_t nc) {
-    static_assert(WPT == 1 || (N == 8 && 64 * WPT <= kMixBlock), "several waves per token: n = 8 only");
-    using W = MixWalk<WPT>;
-    constexpr int E = MixChunk<DX>::E;
-    const int lane = threadIdx.x & 63;
-    const int64_t stride = W::token_stride();
-    const int64_t cfirst = W::first_chunk();
-    int64_t t = W::first_token();
-    if (t >= B) return;  // uniform over the block when WPT > 1
-    // per-wave sums of the token's dP (WPT > 1), two buffers by token parity: a wave writes
-    // buffer q for token k + 2 only after the barrier of token k + 1, which the first wave
-    // reaches after it has read buffer q for token k
-    __shared__ float part[WPT > 1 ? 2 * WPT * 64 : 1];
-    int parity = 0;
-    constexpr int NN = N * N;
-    float p[NN], acc[NN];  // acc: this lane's part of dP_ij = sum_c dY_i[c] X_j[c]
-    auto token_matrix = [&](int64_t tt) { load_token_matrix<N>(P, tt, p); };
-    // dH of token t from the lanes' partial dP (uniform branch: every lane takes part)
-    // (n = 8: dP itself, lane L writing entry L, for the 8 x 8 backward to take over)
-    auto finish_token = [&]() {
-        if constexpr (N == 4) {
-            float G[16], out[16];
-            wave_sum16(acc, lane, G);
-            implicit_vjp(p, G, out);
-            if (lane < 4) {
-                const v4f row = lane == 0 ? v4f{out[0], out[1], out[2], out[3]}
-                              : lane == 1 ? v4f{out[4], out[5], out[6], out[7]}
-                              : lane == 2 ? v4f{out[8], out[9], out[10], out[11]}
-                                          : v4f{out[12], out[13], out[14], out[15]};
-                reinterpret_cast<v4f*>(dH)[4 * t + lane] = row;
-            }
-        } else if constexpr (WPT == 1) {
-            dH[64 * t + lane] = wave_sum64_own(acc, lane);
+            for (int k = 0; k < NV / 2; ++k) out[k] = h[k];
         } else {
-            float* buf = part + parity * (WPT * 64);
-            const int w = W::wave();
-            buf[64 * w + lane] = wave_sum64_own(acc, lane);
-            // LDS-only fences: the next item's global loads stay in flight across the barrier
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-            if (w == 0) {
-                float sum = buf[lane];
-#pragma unroll
-                for (int q = 1; q < WPT; ++q) sum += buf[64 * q + lane];
-                dH[64 * t + lane] = sum;
-            }
-            parity ^= 1;
+            lane_sums<M / 2, NV / 2>(h, out, lane);
         }
+    }
+}
+
+// acc_ij += sum_c g_i[c] x_j[c] over one chunk of each row, one 32-bit word at a time.
+template <int DX, int N>
+__device__ __forceinline__ void add_outer(const v4u x[N], const v4u g[N], float acc[N * N]) {
+    constexpr int EW = MixChunk<DX>::E / 4;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        if constexpr (DX == BIRKHOFF4_BF16) {
+            // two channels per word: bf16 dot products accumulated in fp32 (the products of two
+            // bf16 values are exact in fp32), on the packed words as loaded
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+#pragma unroll
+                for (int j = 0; j < N; ++j)
+                    acc[N * i + j] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, static_cast<uint32_t>(g[i][w])),
+                                                                     __builtin_bit_cast(bf16x2, static_cast<uint32_t>(x[j][w])),
+                                                                     acc[N * i + j], false);
+        } else {
+            float xv[N][EW], gv[N][EW];
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                unpack_word<DX>(x[j], w, xv[j]);
+                unpack_word<DX>(g[j], w, gv[j]);
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+#pragma unroll
+                for (int j = 0; j < N; ++j)
+#pragma unroll
+                    for (int e = 0; e < EW; ++e) acc[N * i + j] = __builtin_fmaf(gv[i][e], xv[j][e], acc[N * i + j]);
+        }
+    }
+}
+
+// Row `i` (a lane index) of a 4 x 4 matrix held whole by the lane.
+__device__ __forceinline__ v4f pick_row4(const float m[16], int i) {
+    return i == 0   ? v4f{m[0], m[1], m[2], m[3]}
+           : i == 1 ? v4f{m[4], m[5], m[6], m[7]}
+           : i == 2 ? v4f{m[8], m[9], m[10], m[11]}
+                    : v4f{m[12], m[13], m[14], m[15]};
+}
+
+// Backward. A block takes a token, its W waves the columns of the row in turn: dX is written
+// column by column and each lane gathers its part of dP_ij = sum_c dY_i[c] X_j[c]. Each wave
+// sums its lanes' parts; with W > 1 the waves leave them in LDS and the first one adds them
+// in wave order, so the result does not depend on timing. For n = 4 it then forms dH; for n =
+// 8 it writes dP, lane L entry L, for the 8 x 8 backward to take over.
+constexpr int mix_bwd_max_waves(int n) { return n == 8 ? 4 : 8; }
+
+template <int DX, int N>
+__global__ __launch_bounds__(64 * mix_bwd_max_waves(N)) void mix_bwd_kernel(const float* __restrict__ P,
+                                                                           const v4u* __restrict__ X,
+                                                                           const v4u* __restrict__ dY,
+                                                                           v4u* __restrict__ dX, float* __restrict__ dH,
+                                                                           int64_t B, int64_t nc, int win) {
+    constexpr int NN = N * N;
+    __shared__ float part[mix_bwd_max_waves(N) * NN];  // [wave][entry]
+    const unsigned lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int W = blockDim.x >> 6;
+    for (int64_t k = blockIdx.x; k < B; k += gridDim.x) {
+        const int64_t t = mix_token(k, B, win);
+        float p[NN], acc[NN];
 #pragma unroll
         for (int q = 0; q < NN; ++q) acc[q] = 0.f;
-    };
+        for (int64_t col = 64 * w; col < nc; col += 64 * W) {
+            const int64_t off = N * nc * t + col;  // uniform: scalar row addresses, the lane a 32-bit offset
+            const bool own = lane < nc - col;
+            int64_t nr = nc;  // opaque: rows are stepped to here, not kept as 3 N addresses over the loop
+            asm volatile("" : "+s"(nr));
+            v4u x[N], g[N], o[N];
 #pragma unroll
-    for (int q = 0; q < NN; ++q) acc[q] = 0.f;
-    token_matrix(t);
-    if (nc == 0) {  // no channels: dP = 0 (uniform)
-        for (;;) {
-            finish_token();
-            t += stride;
-            if (t >= B) return;
-            token_matrix(t);
-        }
-    }
-    int64_t c0 = cfirst;
-    auto offset = [&](int64_t tt, int64_t cc0) {
-        const int64_t cc = cc0 + lane;
-        return N * nc * tt + (cc < nc ? cc : nc - 1);
-    };
-    auto load_item = [&](int64_t off, v4u x[N], v4u g[N]) {
+            for (int j = 0; j < N; ++j) x[j] = g[j] = v4u{0u, 0u, 0u, 0u};
+            if (own) {
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-            x[j] = __builtin_nontemporal_load(X + off + j * nc);
-            g[j] = __builtin_nontemporal_load(dY + off + j * nc);
-        }
-    };
-    // dX of the item in (xc, gc) and its part of dP
-    auto process = [&](const v4u xc[N], const v4u gc[N]) {
-        v4u o[N];
-        mix_chunk<DX, N, true>(p, gc, o);
-        const int64_t off = offset(t, c0);
+                for (int j = 0; j < N; ++j) x[j] = __builtin_nontemporal_load(X + (off + j * nr) + lane);
 #pragma unroll
-        for (int j = 0; j < N; ++j) __builtin_nontemporal_store(o[j], dX + off + j * nc);
-        const bool own = c0 + lane < nc;
-        constexpr int EW = E / 4;
+                for (int j = 0; j < N; ++j) g[j] = __builtin_nontemporal_load(dY + (off + j * nr) + lane);
+            }
+            load_token_matrix<N>(P, t, p);
+            // dP first: X's registers are then free for dX (three waves per SIMD with n = 8)
+            add_outer<DX, N>(x, g, acc);
+            __builtin_amdgcn_sched_barrier(0);
+            mix_chunk<DX, N, true>(p, g, o);
+            if (own) {
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {  // one 32-bit word of the chunk at a time
-            if constexpr (DX == BIRKHOFF4_BF16) {
-                // two channels per word: bf16 dot products accumulated in fp32 (the products
-                // of two bf16 values are exact in fp32), on the packed words as loaded
-                uint32_t xw[N], gw[N];
-#pragma unroll
-                for (int j = 0; j < N; ++j) {
-                    const v4u xj = own ? xc[j] : v4u{0u, 0u, 0u, 0u};
-                    xw[j] = w == 0 ? xj.x : w == 1 ? xj.y : w == 2 ? xj.z : xj.w;
-                    gw[j] = w == 0 ? gc[j].x : w == 1 ? gc[j].y : w == 2 ? gc[j].z : gc[j].w;
-                }
-#pragma unroll
-                for (int i = 0; i < N; ++i)
-#pragma unroll
-                    for (int j = 0; j < N; ++j)
-                        acc[N * i + j] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, gw[i]),
-                                                                          __builtin_bit_cast(bf16x2, xw[j]),
-                                                                          acc[N * i + j], false);
-            } else {
-                float xv[N][EW], gv[N][EW];
-#pragma unroll
-                for (int j = 0; j < N; ++j) {
-                    unpack_word<DX>(own ? xc[j] : v4u{0u, 0u, 0u, 0u}, w, xv[j]);
-                    unpack_word<DX>(gc[j], w, gv[j]);
-                }
-#pragma unroll
-                for (int i = 0; i < N; ++i)
-#pragma unroll
-                    for (int j = 0; j < N; ++j)
-#pragma unroll
-                        for (int e = 0; e < EW; ++e)
-                            acc[N * i + j] = __builtin_fmaf(gv[i][e], xv[j][e], acc[N * i + j]);
+                for (int j = 0; j < N; ++j) __builtin_nontemporal_store(o[j], dX + (off + j * nr) + lane);
             }
         }
-    };
-    const int64_t items = ((B - t + stride - 1) / stride) * ((nc - cfirst + W::kStep - 1) / W::kStep);
-    // process the item in (xc, gc) while the next one loads into (xn, gn)
-    auto step = [&](const v4u xc[N], const v4u gc[N], v4u xn[N], v4u gn[N]) {
-        int64_t tn = t, cn = c0 + W::kStep;
-        if (cn >= nc) {
-            cn = cfirst;
-            tn = t + stride;
+        // the token's dP: lane L holds entry L (n = 8) or, after the quad sum, L >> 2 (n = 4)
+        const int entry = N == 4 ? lane >> 2 : lane;
+        float own_sum[1];
+        lane_sums<32, NN>(acc, own_sum, lane);
+        float sum = N == 4 ? qsum(own_sum[0]) : own_sum[0];
+        if (W > 1) {  // uniform over the block
+            part[NN * w + entry] = sum;
+            __syncthreads();
+            if (w == 0) {
+                sum = part[entry];
+                for (int q = 1; q < W; ++q) sum += part[NN * q + entry];
+            }
         }
-        const bool more = tn < B;
-        load_item(more ? offset(tn, cn) : offset(t, c0), xn, gn);
-        __builtin_amdgcn_sched_barrier(0);
-        process(xc, gc);
-        if (tn != t) {
-            finish_token();
-            if (more) token_matrix(tn);
+        if (w == 0) {
+            if constexpr (N == 8) {
+                dH[64 * t + lane] = sum;
+            } else {
+                float G[16], out[16];
+#pragma unroll
+                for (int q = 0; q < 16; ++q) G[q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sum), 4 * q));
+                load_token_matrix<N>(P, t, p);
+                implicit_vjp(p, G, out);
+                if (lane < 4) reinterpret_cast<v4f*>(dH)[4 * t + lane] = pick_row4(out, lane);
+            }
         }
-        t = tn;
-        c0 = cn;
-    };
-    // peeled first step and counted loop of two, as in the forward
-    v4u xa[N], ga[N], xb[N], gb[N];
-    load_item(offset(t, c0), xa, ga);
-    step(xa, ga, xb, gb);
-    int64_t k = 1;
-    for (; k + 2 <= items; k += 2) {
-        step(xb, gb, xa, ga);
-        step(xa, ga, xb, gb);
+        if (W > 1 && k + gridDim.x < B) __syncthreads();  // `part` is written again for the next token
     }
-    if (k < items) step(xb, gb, xa, ga);
+}
+
+// Short rows, nc <= L with L = 8, 16 or 32: L lanes per token, 64 / L tokens per wave, one
+// chunk of every row per lane, P read per lane. A wave of its own for each token would leave
+// most lanes idle: MIX_SHORT.
+constexpr int kMixShortBlock = 256;
+
+template <int N>
+__device__ __forceinline__ void load_lane_matrix(const float* __restrict__ P, int64_t t, float p[N * N]) {
+    const v4f* p4 = reinterpret_cast<const v4f*>(P) + N * N / 4 * t;
+#pragma unroll
+    for (int q = 0; q < N * N / 4; ++q) {
+        const v4f r = p4[q];
+        p[4 * q] = r.x; p[4 * q + 1] = r.y; p[4 * q + 2] = r.z; p[4 * q + 3] = r.w;
+    }
+}
+
+template <int DX, int N, int L>
+__global__ __launch_bounds__(kMixShortBlock) void mix_fwd_short_kernel(const float* __restrict__ P,
+                                                                       const v4u* __restrict__ X, v4u* __restrict__ Y,
+                                                                       int64_t B, int nc) {
+    const int c = threadIdx.x % L;
+    for (int64_t t = static_cast<int64_t>(blockIdx.x) * (kMixShortBlock / L) + threadIdx.x / L; t < B;
+         t += static_cast<int64_t>(gridDim.x) * (kMixShortBlock / L)) {
+        if (c >= nc) return;
+        const int64_t off = static_cast<int64_t>(N) * nc * t + c;
+        v4u x[N], y[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) x[j] = __builtin_nontemporal_load(X + off + j * nc);
+        float p[N * N];
+        load_lane_matrix<N>(P, t, p);
+        mix_chunk<DX, N>(p, x, y);
+#pragma unroll
+        for (int j = 0; j < N; ++j) __builtin_nontemporal_store(y[j], Y + off + j * nc);
+    }
+}
+
+template <int DX, int N, int L>
+__global__ __launch_bounds__(kMixShortBlock) void mix_bwd_short_kernel(const float* __restrict__ P,
+                                                                       const v4u* __restrict__ X,
+                                                                       const v4u* __restrict__ dY,
+                                                                       v4u* __restrict__ dX, float* __restrict__ dH,
+                                                                       int64_t B, int nc) {
+    constexpr int NN = N * N;
+    const int c = threadIdx.x % L;
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * (kMixShortBlock / L);
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * (kMixShortBlock / L);
+    for (int64_t base = first; base < B; base += stride) {  // uniform over the block: every lane takes part in the sums
+        const int64_t t = base + threadIdx.x / L;
+        const bool valid = t < B, own = valid && c < nc;
+        const int64_t off = static_cast<int64_t>(N) * nc * t + c;
+        v4u x[N], g[N], o[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) x[j] = g[j] = v4u{0u, 0u, 0u, 0u};
+        if (own) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) x[j] = __builtin_nontemporal_load(X + off + j * nc);
+#pragma unroll
+            for (int j = 0; j < N; ++j) g[j] = __builtin_nontemporal_load(dY + off + j * nc);
+        }
+        float p[NN], acc[NN];
+#pragma unroll
+        for (int q = 0; q < NN; ++q) p[q] = acc[q] = 0.f;
+        if (valid) load_lane_matrix<N>(P, t, p);
+        mix_chunk<DX, N, true>(p, g, o);
+        if (own) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) __builtin_nontemporal_store(o[j], dX + off + j * nc);
+        }
+        add_outer<DX, N>(x, g, acc);
+        if constexpr (N == 8) {
+            constexpr int NE = 64 / L;  // entries of dP per lane
+            float d[NE];
+            lane_sums<L / 2, 64>(acc, d, threadIdx.x);
+            if (valid) {
+#pragma unroll
+                for (int q = 0; q < NE; ++q) dH[64 * t + NE * c + q] = d[q];
+            }
+        } else {
+            // every lane of the token needs the sixteen sums: butterflies over its L lanes
+            float G[16], out[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                float s = gsum_lanes<8>(acc[q]);
+                if constexpr (L >= 16)
+                    s += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s), 0x128, 0xF, 0xF, true));  // row_ror:8
+                if constexpr (L >= 32) {
+                    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+                    s = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+                }
+                G[q] = s;
+            }
+            implicit_vjp(p, G, out);
+            if (valid && c < 4) reinterpret_cast<v4f*>(dH)[4 * t + c] = pick_row4(out, c);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1836,13 +1858,6 @@ __device__ __forceinline__ void decode_row8(const uint32_t w[RawWords8<DT>::n], 
 #pragma unroll
         for (int k = 0; k < 8; ++k) h[k] = __uint_as_float(w[8 * r + k]);
     }
-}
-
-// Sum over the two lanes of a pair (2k, 2k + 1); both receive the same value (the add
-// commutes, and contraction is off so that it is not fused into the caller's product).
-__device__ __forceinline__ float psum(float x) {
-#pragma clang fp contract(off)
-    return x + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, true));
 }
 
 // The OT stopping test: |c_j - b_j| <= tol max(1, sum a / 8, b_j) for every column: absolute
@@ -2312,18 +2327,6 @@ __global__ __launch_bounds__(kB8Block, 2) void newton8_fwd_kernel(const void* __
 // 8 R problems until the slowest is done, and a block is one wave, so that small batches reach
 // every CU. The iteration is the throughput kernel's. Bound: the dependent chain of a trial
 // (about 1.3 us with one row per lane against 2.7 us for one problem per lane).
-
-// Sum over a group of G lanes, the same value in all of them (contraction off as in qsum):
-// partners (1,0,3,2), then (2,3,0,1), then, with eight lanes, the other quad by a mirror.
-template <int G>
-__device__ __forceinline__ float gsum_lanes(float x) {
-#pragma clang fp contract(off)
-    if constexpr (G == 2) return psum(x);
-    x = qsum(x);
-    if constexpr (G == 8)
-        x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x141, 0xF, 0xF, true));  // row_half_mirror
-    return x;
-}
 
 constexpr int kGrp8Block = 64;
 
@@ -3460,43 +3463,85 @@ int launch_bwd8(Kernel kern, const float* P, const void* dP, void* dH, int64_t B
     return launch_status();
 }
 
-// Residual mixing, grid-stride over the tokens: one token per wave at a time for n = 4, and
-// for n = 8 one token per block of kMix8Wpt waves once every row has at least one chunk per
-// wave, nc >= 64 kMix8Wpt, which the backward's per-token barrier needs. Both layouts size
-// the grid for the same number of waves per CU.
-template <int N>
-bool mix_block_per_token(int64_t nc) {
-    return N == 8 && nc >= 64 * kMix8Wpt;
-}
+// Residual mixing: block and grid. A row is `cols` columns of 64 chunks, one per wave, up to
+// `most` waves per block; more columns are spread evenly over shares of the row (forward) or
+// turns of the block's waves (backward). Measured lines (us, bf16 unless said):
+//  * n = 4 forward, up to 16 waves: 2 * 10^4 tokens of 4 x 6144 (12 columns) 317 with 12 waves,
+//    360 with 6, 351 with 4; 2^14 tokens of 4 x 4096 fp32 (16) 341 with 16, 367 with 8.
+//  * n = 4 backward, up to 8: 2 * 10^4 tokens of 4 x 4608 (9 columns) 359 in two turns, 395
+//    with 9 waves; 4 x 5632 431 and 466; 4 x 7680 (15) 622 and 602; 4 x 8192 634 and 641.
+//  * n = 8 forward, up to 8 columns; wider rows in blocks of 4: 10^4 tokens of 8 x 6144 365 with
+//    4 waves, 376 with 6; 2^13 of 8 x 4096 fp32 366 with 4, 374 with 8.
+//  * n = 8 backward, up to 4: its registers leave two waves per SIMD, so a larger block leaves a
+//    CU with one: 2^14 tokens of 8 x 4096 514 with 4 waves, 608 with 8; 16000 of 8 x 2560 (5
+//    columns) 348 with 3, 500 with 5.
+//  * One column per row: in the forward four tokens share a block (two with n = 8): 3 * 10^4
+//    tokens of 4 x 504 40.2, alone 41.3; in the backward they don't: 58.3, shared 61.3.
+//  * XCD windows of 16 tokens: 2^15 tokens of 4 x 4096 forward 384 -> 344 and backward 536 ->
+//    517, 2^14 of 8 x 4096 forward 365 -> 346; none for the n = 8 backward and wide n = 8 rows (8 x
+//    4096 fp32 backward 522, with windows 557).
+constexpr int64_t kMixMaxGrid = int64_t(1) << 20;  // blocks over tokens; further tokens loop
+constexpr int64_t kMixMaxShares = 32768;           // blocks over a row; further columns loop
+constexpr int64_t kMixShortRow = 32;               // chunks: rows up to this take the short-row kernels
 
 struct MixLaunch {
-    int64_t grid;
-    unsigned threads;
+    dim3 grid, block;
+    int win;  // tokens in an XCD's window
 };
 
-template <int N>
-MixLaunch mix_launch(int64_t B, int64_t nc, int cus) {
-    if (mix_block_per_token<N>(nc))
-        return {grid_for(B, 1, cus, kMixPerCu * kMixWaves / kMix8Wpt), MixWalk<kMix8Wpt>::kBlockThreads};
-    return {grid_for(B, kMixWaves, cus, kMixPerCu), kMixBlock};
+MixLaunch mix_launch(int64_t B, int64_t nc, int n, bool backward) {
+    const int64_t cols = nc > 0 ? (nc + 63) / 64 : 1;
+    const bool wide8 = n == 8 && cols > 8;
+    const int64_t most = n == 4 ? (backward ? 8 : kMixMaxWaves) : (backward || wide8 ? 4 : 8);
+    const int64_t turns = (cols + most - 1) / most;
+    const int64_t waves = (cols + turns - 1) / turns;
+    const unsigned tokens = waves > 1 || backward ? 1 : n == 4 ? 4 : 2;
+    const int64_t count = (B + tokens - 1) / tokens;
+    const int64_t shares = backward ? 1 : (turns < kMixMaxShares ? turns : kMixMaxShares);
+    return {dim3(static_cast<unsigned>(count < kMixMaxGrid ? count : kMixMaxGrid), static_cast<unsigned>(shares)),
+            dim3(static_cast<unsigned>(64 * waves), tokens), n == 8 && (backward || wide8) ? 1 : 16};
+}
+
+unsigned mix_short_grid(int64_t B, int lanes) {
+    const int64_t per = kMixShortBlock / lanes, want = (B + per - 1) / per;
+    return static_cast<unsigned>(want < kMixMaxGrid ? want : kMixMaxGrid);
 }
 
 template <int DX, int N = 4>
-int launch_mix_fwd(const float* P, const void* X, void* Y, int64_t B, int64_t nc, hipStream_t stream, int cus) {
-    const MixLaunch l = mix_launch<N>(B, nc, cus);
-    auto kern = mix_block_per_token<N>(nc) ? mix_fwd_kernel<DX, N, N == 8 ? kMix8Wpt : 1> : mix_fwd_kernel<DX, N, 1>;
-    launch_kernel(kern, dim3(static_cast<unsigned>(l.grid)), dim3(l.threads), 0, stream, P,
-                  static_cast<const v4u*>(X), static_cast<v4u*>(Y), B, nc);
+int launch_mix_fwd(const float* P, const void* X, void* Y, int64_t B, int64_t nc, hipStream_t stream) {
+    const v4u* x = static_cast<const v4u*>(X);
+    v4u* y = static_cast<v4u*>(Y);
+    // (the 64 entries of P that each lane of an 8-stream token reads cost more than idle lanes
+    // once only two tokens share a wave: 3 * 10^4 tokens of 32 chunks 62 us, a wave each 46 us)
+    if (nc <= (N == 4 ? kMixShortRow : 16)) {
+        const int L = nc <= 8 ? 8 : nc <= 16 ? 16 : 32;
+        auto kern = L == 8 ? mix_fwd_short_kernel<DX, N, 8> : mix_fwd_short_kernel<DX, N, 16>;
+        if constexpr (N == 4)
+            if (L == 32) kern = mix_fwd_short_kernel<DX, N, 32>;
+        launch_kernel(kern, dim3(mix_short_grid(B, L)), dim3(kMixShortBlock), 0, stream, P, x, y, B,
+                      static_cast<int>(nc));
+        return launch_status();
+    }
+    const MixLaunch l = mix_launch(B, nc, N, false);
+    launch_kernel((mix_fwd_kernel<DX, N>), l.grid, l.block, 0, stream, P, x, y, B, nc, l.win);
     return launch_status();
 }
 
 template <int DX, int N = 4>
 int launch_mix_bwd(const float* P, const void* X, const void* dY, void* dX, float* dH, int64_t B, int64_t nc,
-                   hipStream_t stream, int cus) {
-    const MixLaunch l = mix_launch<N>(B, nc, cus);
-    auto kern = mix_block_per_token<N>(nc) ? mix_bwd_kernel<DX, N, N == 8 ? kMix8Wpt : 1> : mix_bwd_kernel<DX, N, 1>;
-    launch_kernel(kern, dim3(static_cast<unsigned>(l.grid)), dim3(l.threads), 0, stream, P,
-                  static_cast<const v4u*>(X), static_cast<const v4u*>(dY), static_cast<v4u*>(dX), dH, B, nc);
+                   hipStream_t stream) {
+    const v4u *x = static_cast<const v4u*>(X), *dy = static_cast<const v4u*>(dY);
+    v4u* dx = static_cast<v4u*>(dX);
+    if (nc <= kMixShortRow) {  // nc = 0 too: dP = 0
+        const int L = nc <= 8 ? 8 : nc <= 16 ? 16 : 32;
+        auto kern = L == 8 ? mix_bwd_short_kernel<DX, N, 8>
+                           : L == 16 ? mix_bwd_short_kernel<DX, N, 16> : mix_bwd_short_kernel<DX, N, 32>;
+        launch_kernel(kern, dim3(mix_short_grid(B, L)), dim3(kMixShortBlock), 0, stream, P, x, dy, dx, dH, B,
+                      static_cast<int>(nc));
+        return launch_status();
+    }
+    const MixLaunch l = mix_launch(B, nc, N, true);
+    launch_kernel((mix_bwd_kernel<DX, N>), l.grid, l.block, 0, stream, P, x, dy, dx, dH, B, nc, l.win);
     return launch_status();
 }
 
@@ -3817,13 +3862,11 @@ int birkhoff4_mix_fwd(const void* H, int h_dtype, const void* X, int x_dtype, vo
         overlaps(H, nh, iters, ni) || overlaps(P, np, dual, nd) || overlaps(P, np, iters, ni) ||
         overlaps(dual, nd, iters, ni))
         return BIRKHOFF4_ERR_OVERLAP;
-    int cus = 0, dev = 0;
-    if (int e = device_cus(stream, &cus, &dev)) return e;
     // the projection checks and queues P first; the mixing kernel then reads it
     if (int e = birkhoff4_fwd_ex2(H, h_dtype, P, dual, iters, B, tol, max_iter, BIRKHOFF4_AUTO, stream)) return e;
     if (nc == 0) return BIRKHOFF4_OK;
-    if (x_dtype == BIRKHOFF4_BF16) return launch_mix_fwd<BIRKHOFF4_BF16>(P, X, Y, B, nc, stream, cus);
-    return launch_mix_fwd<BIRKHOFF4_F32>(P, X, Y, B, nc, stream, cus);
+    if (x_dtype == BIRKHOFF4_BF16) return launch_mix_fwd<BIRKHOFF4_BF16>(P, X, Y, B, nc, stream);
+    return launch_mix_fwd<BIRKHOFF4_F32>(P, X, Y, B, nc, stream);
 }
 
 int birkhoff4_mix_bwd(const float* P, const void* X, const void* dY, int x_dtype, void* dX, float* dH, int64_t B,
@@ -3842,10 +3885,8 @@ int birkhoff4_mix_bwd(const float* P, const void* X, const void* dY, int x_dtype
     if (overlaps(dX, nx, P, np) || overlaps(dX, nx, X, nx) || overlaps(dX, nx, dY, nx) || overlaps(dX, nx, dH, np) ||
         overlaps(dH, np, P, np) || overlaps(dH, np, X, nx) || overlaps(dH, np, dY, nx))
         return BIRKHOFF4_ERR_OVERLAP;
-    int cus = 0, dev = 0;
-    if (int e = device_cus(stream, &cus, &dev)) return e;
-    if (x_dtype == BIRKHOFF4_BF16) return launch_mix_bwd<BIRKHOFF4_BF16>(P, X, dY, dX, dH, B, nc, stream, cus);
-    return launch_mix_bwd<BIRKHOFF4_F32>(P, X, dY, dX, dH, B, nc, stream, cus);
+    if (x_dtype == BIRKHOFF4_BF16) return launch_mix_bwd<BIRKHOFF4_BF16>(P, X, dY, dX, dH, B, nc, stream);
+    return launch_mix_bwd<BIRKHOFF4_F32>(P, X, dY, dX, dH, B, nc, stream);
 }
 
 int birkhoff8_mix_fwd(const void* H, int h_dtype, const void* X, int x_dtype, void* Y, float* P, float* dual,
@@ -3871,12 +3912,10 @@ int birkhoff8_mix_fwd(const void* H, int h_dtype, const void* X, int x_dtype, vo
         overlaps(H, nh, iters, ni) || overlaps(P, np, dual, nd) || overlaps(P, np, iters, ni) ||
         overlaps(dual, nd, iters, ni))
         return BIRKHOFF4_ERR_OVERLAP;
-    int cus = 0, dev = 0;
-    if (int e = device_cus(stream, &cus, &dev)) return e;
     if (int e = birkhoff8_fwd(H, h_dtype, P, dual, iters, B, tol, max_iter, stream)) return e;
     if (nc == 0) return BIRKHOFF4_OK;
-    if (x_dtype == BIRKHOFF4_BF16) return launch_mix_fwd<BIRKHOFF4_BF16, 8>(P, X, Y, B, nc, stream, cus);
-    return launch_mix_fwd<BIRKHOFF4_F32, 8>(P, X, Y, B, nc, stream, cus);
+    if (x_dtype == BIRKHOFF4_BF16) return launch_mix_fwd<BIRKHOFF4_BF16, 8>(P, X, Y, B, nc, stream);
+    return launch_mix_fwd<BIRKHOFF4_F32, 8>(P, X, Y, B, nc, stream);
 }
 
 int birkhoff8_mix_bwd(const float* P, const void* X, const void* dY, int x_dtype, void* dX, float* dH, int64_t B,
@@ -3895,12 +3934,10 @@ int birkhoff8_mix_bwd(const float* P, const void* X, const void* dY, int x_dtype
     if (overlaps(dX, nx, P, np) || overlaps(dX, nx, X, nx) || overlaps(dX, nx, dY, nx) || overlaps(dX, nx, dH, np) ||
         overlaps(dH, np, P, np) || overlaps(dH, np, X, nx) || overlaps(dH, np, dY, nx))
         return BIRKHOFF4_ERR_OVERLAP;
-    int cus = 0, dev = 0;
-    if (int e = device_cus(stream, &cus, &dev)) return e;
     // dX, and dP into dH's memory; then the 8 x 8 backward turns dP into dH in place (each of
     // its waves reads a chunk's dP whole before it writes that chunk's dH)
-    const int e = x_dtype == BIRKHOFF4_BF16 ? launch_mix_bwd<BIRKHOFF4_BF16, 8>(P, X, dY, dX, dH, B, nc, stream, cus)
-                                            : launch_mix_bwd<BIRKHOFF4_F32, 8>(P, X, dY, dX, dH, B, nc, stream, cus);
+    const int e = x_dtype == BIRKHOFF4_BF16 ? launch_mix_bwd<BIRKHOFF4_BF16, 8>(P, X, dY, dX, dH, B, nc, stream)
+                                            : launch_mix_bwd<BIRKHOFF4_F32, 8>(P, X, dY, dX, dH, B, nc, stream);
     if (e) return e;
     return launch_bwd8(implicit8_bwd_kernel<BIRKHOFF4_F32, BIRKHOFF4_F32, false, true>, P, dH, dH, B, stream);
 }
