@@ -265,6 +265,10 @@ int birkhoff4_mix_fwd(const void* H, int h_dtype, const void* X, int x_dtype, vo
 int birkhoff4_mix_bwd(const float* P, const void* X, const void* dY, int x_dtype, void* dX, float* dH, int64_t B,
                       int64_t C, hipStream_t stream);
 
+/* birkhoff4_mix_bwd with a storage dtype for dH (as in birkhoff4_bwd_ex2). */
+int birkhoff4_mix_bwd_ex(const float* P, const void* X, const void* dY, int x_dtype, void* dX, void* dH, int dh_dtype,
+                         int64_t B, int64_t C, hipStream_t stream);
+
 /* Residual mixing with n = 8 streams per token: birkhoff4_mix_fwd / birkhoff4_mix_bwd with the
  * 8 x 8 projection (birkhoff8_fwd / birkhoff8_bwd). H and P are [B][8][8], X, Y, dY, dX are
  * [B][8][C] (stream i of token b starts at element (8 b + i) C), dual [B][16] and iters as for
@@ -274,6 +278,12 @@ int birkhoff8_mix_fwd(const void* H, int h_dtype, const void* X, int x_dtype, vo
                       int32_t* iters, int64_t B, int64_t C, float tol, int max_iter, hipStream_t stream);
 int birkhoff8_mix_bwd(const float* P, const void* X, const void* dY, int x_dtype, void* dX, float* dH, int64_t B,
                       int64_t C, hipStream_t stream);
+
+/* birkhoff8_mix_bwd with a storage dtype for dH. dP [B][8][8] fp32 is an output too: dL/dP,
+ * from which dH is formed; with an fp32 dH it may be dH's own memory, and must not overlap
+ * anything otherwise. */
+int birkhoff8_mix_bwd_ex(const float* P, const void* X, const void* dY, int x_dtype, void* dX, float* dP, void* dH,
+                         int dh_dtype, int64_t B, int64_t C, hipStream_t stream);
 
 /* Human-readable text for a return code (static storage). */
 const char* birkhoff4_strerror(int code);

@@ -71,6 +71,8 @@ def _load():
         "birkhoff8_ot_bwd": [vp, vp, vp, f32, vp, i64, st],
         "birkhoff4_mix_fwd": [vp, i32, vp, i32, vp, vp, vp, vp, i64, i64, f32, i32, st],
         "birkhoff4_mix_bwd": [vp, vp, vp, i32, vp, vp, i64, i64, st],
+        "birkhoff4_mix_bwd_ex": [vp, vp, vp, i32, vp, vp, i32, i64, i64, st],
+        "birkhoff8_mix_bwd_ex": [vp, vp, vp, i32, vp, vp, vp, i32, i64, i64, st],
         "birkhoff8_mix_fwd": [vp, i32, vp, i32, vp, vp, vp, vp, i64, i64, f32, i32, st],
         "birkhoff8_mix_bwd": [vp, vp, vp, i32, vp, vp, i64, i64, st],
         "birkhoff4_version": [],
@@ -441,7 +443,8 @@ def _mix_fwd(n, H, X, tol, max_iter, want_dual, want_iters):
     return Y, P, dual, iters
 
 
-def _mix_bwd(n, P, X, dY):
+def _mix_bwd(n, P, X, dY, dtype=torch.float32):
+    """(dX like X, dH stored as dtype)."""
     B = _batch(P, "P", n)
     if P.dtype != torch.float32:
         raise TypeError("P must be float32")
@@ -451,10 +454,15 @@ def _mix_bwd(n, P, X, dY):
         raise ValueError("dY must have the shape and dtype of X")
     _same_device(P, X, dY)
     dX = torch.empty_like(X)
-    dH = torch.empty(P.shape, dtype=torch.float32, device=P.device)
-    fn = _load().birkhoff4_mix_bwd if n == 4 else _load().birkhoff8_mix_bwd
+    dH = torch.empty(P.shape, dtype=dtype, device=P.device)
     with torch.cuda.device(P.device):
-        _check(fn(_ptr(P), _ptr(X), _ptr(dY), _dtype_code(X), _ptr(dX), _ptr(dH), B, C, _stream(P)))
+        if n == 4:
+            _check(_load().birkhoff4_mix_bwd_ex(_ptr(P), _ptr(X), _ptr(dY), _dtype_code(X), _ptr(dX), _ptr(dH),
+                                                _dtype_code(dH), B, C, _stream(P)))
+        else:  # dL/dP in fp32 on the way, in dH's own memory if that is fp32
+            dP = dH if dtype == torch.float32 else torch.empty(P.shape, dtype=torch.float32, device=P.device)
+            _check(_load().birkhoff8_mix_bwd_ex(_ptr(P), _ptr(X), _ptr(dY), _dtype_code(X), _ptr(dX), _ptr(dP),
+                                                _ptr(dH), _dtype_code(dH), B, C, _stream(P)))
     return dX, dH
 
 
@@ -501,8 +509,8 @@ class MixFn(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dY):
         P, X = ctx.saved_tensors
-        dX, dH = _mix_bwd(ctx.n, P, X, dY.contiguous().to(X.dtype))
-        return dH.to(ctx.h_dtype), dX, None, None
+        dX, dH = _mix_bwd(ctx.n, P, X, dY.contiguous().to(X.dtype), ctx.h_dtype)
+        return dH, dX, None, None
 
 
 def mix(H: torch.Tensor, X: torch.Tensor, tol: float = DEFAULT_TOL, max_iter: int = DEFAULT_MAX_ITER) -> torch.Tensor:

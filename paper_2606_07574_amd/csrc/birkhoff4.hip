@@ -1289,12 +1289,17 @@ __device__ __forceinline__ void add_outer(const v4u x[N], const v4u g[N], float 
     }
 }
 
-// Row `i` (a lane index) of a 4 x 4 matrix held whole by the lane.
-__device__ __forceinline__ v4f pick_row4(const float m[16], int i) {
-    return i == 0   ? v4f{m[0], m[1], m[2], m[3]}
-           : i == 1 ? v4f{m[4], m[5], m[6], m[7]}
-           : i == 2 ? v4f{m[8], m[9], m[10], m[11]}
-                    : v4f{m[12], m[13], m[14], m[15]};
+// Row `i` (a lane index) of token t's 4 x 4 dH, which the lane holds whole, stored as fp32 or
+// rounded to nearest even as bf16.
+__device__ __forceinline__ void store_dh_row(void* dH, bool h16, int64_t t, int i, const float m[16]) {
+    const v4f r = i == 0   ? v4f{m[0], m[1], m[2], m[3]}
+                  : i == 1 ? v4f{m[4], m[5], m[6], m[7]}
+                  : i == 2 ? v4f{m[8], m[9], m[10], m[11]}
+                           : v4f{m[12], m[13], m[14], m[15]};
+    if (h16)  // uniform
+        reinterpret_cast<uint2*>(dH)[4 * t + i] = uint2{pack_bf16(r.x, r.y), pack_bf16(r.z, r.w)};
+    else
+        reinterpret_cast<v4f*>(dH)[4 * t + i] = r;
 }
 
 // Backward. A block takes a token, its W waves the columns of the row in turn: dX is written
@@ -1302,14 +1307,14 @@ __device__ __forceinline__ v4f pick_row4(const float m[16], int i) {
 // sums its lanes' parts; with W > 1 the waves leave them in LDS and the first one adds them
 // in wave order, so the result does not depend on timing. For n = 4 it then forms dH; for n =
 // 8 it writes dP, lane L entry L, for the 8 x 8 backward to take over.
-constexpr int mix_bwd_max_waves(int n) { return n == 8 ? 4 : 8; }
+constexpr int mix_bwd_max_waves(int n) { return n == 8 ? 4 : kMixMaxWaves; }
 
 template <int DX, int N>
 __global__ __launch_bounds__(64 * mix_bwd_max_waves(N)) void mix_bwd_kernel(const float* __restrict__ P,
                                                                            const v4u* __restrict__ X,
                                                                            const v4u* __restrict__ dY,
-                                                                           v4u* __restrict__ dX, float* __restrict__ dH,
-                                                                           int64_t B, int64_t nc, int win) {
+                                                                           v4u* __restrict__ dX, void* __restrict__ dH,
+                                                                           int64_t B, int64_t nc, int win, bool h16) {
     constexpr int NN = N * N;
     __shared__ float part[mix_bwd_max_waves(N) * NN];  // [wave][entry]
     const unsigned lane = threadIdx.x & 63;
@@ -1359,14 +1364,14 @@ __global__ __launch_bounds__(64 * mix_bwd_max_waves(N)) void mix_bwd_kernel(cons
         }
         if (w == 0) {
             if constexpr (N == 8) {
-                dH[64 * t + lane] = sum;
+                static_cast<float*>(dH)[64 * t + lane] = sum;
             } else {
                 float G[16], out[16];
 #pragma unroll
                 for (int q = 0; q < 16; ++q) G[q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sum), 4 * q));
                 load_token_matrix<N>(P, t, p);
                 implicit_vjp(p, G, out);
-                if (lane < 4) reinterpret_cast<v4f*>(dH)[4 * t + lane] = pick_row4(out, lane);
+                if (lane < 4) store_dh_row(dH, h16, t, lane, out);
             }
         }
         if (W > 1 && k + gridDim.x < B) __syncthreads();  // `part` is written again for the next token
@@ -1412,8 +1417,8 @@ template <int DX, int N, int L>
 __global__ __launch_bounds__(kMixShortBlock) void mix_bwd_short_kernel(const float* __restrict__ P,
                                                                        const v4u* __restrict__ X,
                                                                        const v4u* __restrict__ dY,
-                                                                       v4u* __restrict__ dX, float* __restrict__ dH,
-                                                                       int64_t B, int nc) {
+                                                                       v4u* __restrict__ dX, void* __restrict__ dH,
+                                                                       int64_t B, int nc, bool h16) {
     constexpr int NN = N * N;
     const int c = threadIdx.x % L;
     const int64_t first = static_cast<int64_t>(blockIdx.x) * (kMixShortBlock / L);
@@ -1447,7 +1452,7 @@ __global__ __launch_bounds__(kMixShortBlock) void mix_bwd_short_kernel(const flo
             lane_sums<L / 2, 64>(acc, d, threadIdx.x);
             if (valid) {
 #pragma unroll
-                for (int q = 0; q < NE; ++q) dH[64 * t + NE * c + q] = d[q];
+                for (int q = 0; q < NE; ++q) static_cast<float*>(dH)[64 * t + NE * c + q] = d[q];
             }
         } else {
             // every lane of the token needs the sixteen sums: butterflies over its L lanes
@@ -1464,7 +1469,7 @@ __global__ __launch_bounds__(kMixShortBlock) void mix_bwd_short_kernel(const flo
                 G[q] = s;
             }
             implicit_vjp(p, G, out);
-            if (valid && c < 4) reinterpret_cast<v4f*>(dH)[4 * t + c] = pick_row4(out, c);
+            if (valid && c < 4) store_dh_row(dH, h16, t, c, out);
         }
     }
 }
@@ -3468,8 +3473,9 @@ int launch_bwd8(Kernel kern, const float* P, const void* dP, void* dH, int64_t B
 // turns of the block's waves (backward). Measured lines (us, bf16 unless said):
 //  * n = 4 forward, up to 16 waves: 2 * 10^4 tokens of 4 x 6144 (12 columns) 317 with 12 waves,
 //    360 with 6, 351 with 4; 2^14 tokens of 4 x 4096 fp32 (16) 341 with 16, 367 with 8.
-//  * n = 4 backward, up to 8: 2 * 10^4 tokens of 4 x 4608 (9 columns) 359 in two turns, 395
-//    with 9 waves; 4 x 5632 431 and 466; 4 x 7680 (15) 622 and 602; 4 x 8192 634 and 641.
+//  * n = 4 backward, up to 8, and 15 or 16 columns whole: 2 * 10^4 tokens of 4 x 4608 (9 columns)
+//    359 in two turns, 395 with 9 waves; 4 x 5632 431 and 466; 4 x 7168 (14) 557 and 571; 4 x
+//    7680 622 and 602; 4 x 8192 634 and 641; 2^14 tokens of 4 x 4096 fp32 (16) 530 and 498.
 //  * n = 8 forward, up to 8 columns; wider rows in blocks of 4: 10^4 tokens of 8 x 6144 365 with
 //    4 waves, 376 with 6; 2^13 of 8 x 4096 fp32 366 with 4, 374 with 8.
 //  * n = 8 backward, up to 4: its registers leave two waves per SIMD, so a larger block leaves a
@@ -3492,7 +3498,8 @@ struct MixLaunch {
 MixLaunch mix_launch(int64_t B, int64_t nc, int n, bool backward) {
     const int64_t cols = nc > 0 ? (nc + 63) / 64 : 1;
     const bool wide8 = n == 8 && cols > 8;
-    const int64_t most = n == 4 ? (backward ? 8 : kMixMaxWaves) : (backward || wide8 ? 4 : 8);
+    const bool whole = !backward || (cols > 14 && cols <= kMixMaxWaves);
+    const int64_t most = n == 4 ? (whole ? kMixMaxWaves : 8) : (backward || wide8 ? 4 : 8);
     const int64_t turns = (cols + most - 1) / most;
     const int64_t waves = (cols + turns - 1) / turns;
     const unsigned tokens = waves > 1 || backward ? 1 : n == 4 ? 4 : 2;
@@ -3528,7 +3535,7 @@ int launch_mix_fwd(const float* P, const void* X, void* Y, int64_t B, int64_t nc
 }
 
 template <int DX, int N = 4>
-int launch_mix_bwd(const float* P, const void* X, const void* dY, void* dX, float* dH, int64_t B, int64_t nc,
+int launch_mix_bwd(const float* P, const void* X, const void* dY, void* dX, void* dH, bool h16, int64_t B, int64_t nc,
                    hipStream_t stream) {
     const v4u *x = static_cast<const v4u*>(X), *dy = static_cast<const v4u*>(dY);
     v4u* dx = static_cast<v4u*>(dX);
@@ -3537,11 +3544,11 @@ int launch_mix_bwd(const float* P, const void* X, const void* dY, void* dX, floa
         auto kern = L == 8 ? mix_bwd_short_kernel<DX, N, 8>
                            : L == 16 ? mix_bwd_short_kernel<DX, N, 16> : mix_bwd_short_kernel<DX, N, 32>;
         launch_kernel(kern, dim3(mix_short_grid(B, L)), dim3(kMixShortBlock), 0, stream, P, x, dy, dx, dH, B,
-                      static_cast<int>(nc));
+                      static_cast<int>(nc), h16);
         return launch_status();
     }
     const MixLaunch l = mix_launch(B, nc, N, true);
-    launch_kernel((mix_bwd_kernel<DX, N>), l.grid, l.block, 0, stream, P, x, dy, dx, dH, B, nc, l.win);
+    launch_kernel((mix_bwd_kernel<DX, N>), l.grid, l.block, 0, stream, P, x, dy, dx, dH, B, nc, l.win, h16);
     return launch_status();
 }
 
@@ -3869,10 +3876,10 @@ int birkhoff4_mix_fwd(const void* H, int h_dtype, const void* X, int x_dtype, vo
     return launch_mix_fwd<BIRKHOFF4_F32>(P, X, Y, B, nc, stream);
 }
 
-int birkhoff4_mix_bwd(const float* P, const void* X, const void* dY, int x_dtype, void* dX, float* dH, int64_t B,
-                      int64_t C, hipStream_t stream) {
+int birkhoff4_mix_bwd_ex(const float* P, const void* X, const void* dY, int x_dtype, void* dX, void* dH, int dh_dtype,
+                         int64_t B, int64_t C, hipStream_t stream) {
     if (B < 0 || B > (INT64_MAX / 64)) return BIRKHOFF4_ERR_SIZE;
-    if (!dtype_ok(x_dtype)) return BIRKHOFF4_ERR_DTYPE;
+    if (!dtype_ok(x_dtype) || !dtype_ok(dh_dtype)) return BIRKHOFF4_ERR_DTYPE;
     const int64_t E = x_dtype == BIRKHOFF4_BF16 ? 8 : 4;
     if (C < 0 || C % E != 0) return BIRKHOFF4_ERR_CHANNELS;
     const int64_t nc = C / E;
@@ -3881,12 +3888,19 @@ int birkhoff4_mix_bwd(const float* P, const void* X, const void* dY, int x_dtype
     if (!P || !dH || (nc > 0 && (!X || !dY || !dX))) return BIRKHOFF4_ERR_NULL;
     if (misaligned(P) || misaligned(X) || misaligned(dY) || misaligned(dX) || misaligned(dH))
         return BIRKHOFF4_ERR_ALIGN;
-    const size_t np = static_cast<size_t>(B) * 64, nx = static_cast<size_t>(B) * 64 * nc;
-    if (overlaps(dX, nx, P, np) || overlaps(dX, nx, X, nx) || overlaps(dX, nx, dY, nx) || overlaps(dX, nx, dH, np) ||
-        overlaps(dH, np, P, np) || overlaps(dH, np, X, nx) || overlaps(dH, np, dY, nx))
+    const size_t np = static_cast<size_t>(B) * 64, nx = static_cast<size_t>(B) * 64 * nc,
+                 nh = static_cast<size_t>(B) * 16 * dtype_bytes(dh_dtype);
+    if (overlaps(dX, nx, P, np) || overlaps(dX, nx, X, nx) || overlaps(dX, nx, dY, nx) || overlaps(dX, nx, dH, nh) ||
+        overlaps(dH, nh, P, np) || overlaps(dH, nh, X, nx) || overlaps(dH, nh, dY, nx))
         return BIRKHOFF4_ERR_OVERLAP;
-    if (x_dtype == BIRKHOFF4_BF16) return launch_mix_bwd<BIRKHOFF4_BF16>(P, X, dY, dX, dH, B, nc, stream);
-    return launch_mix_bwd<BIRKHOFF4_F32>(P, X, dY, dX, dH, B, nc, stream);
+    const bool h16 = dh_dtype == BIRKHOFF4_BF16;
+    if (x_dtype == BIRKHOFF4_BF16) return launch_mix_bwd<BIRKHOFF4_BF16>(P, X, dY, dX, dH, h16, B, nc, stream);
+    return launch_mix_bwd<BIRKHOFF4_F32>(P, X, dY, dX, dH, h16, B, nc, stream);
+}
+
+int birkhoff4_mix_bwd(const float* P, const void* X, const void* dY, int x_dtype, void* dX, float* dH, int64_t B,
+                      int64_t C, hipStream_t stream) {
+    return birkhoff4_mix_bwd_ex(P, X, dY, x_dtype, dX, dH, BIRKHOFF4_F32, B, C, stream);
 }
 
 int birkhoff8_mix_fwd(const void* H, int h_dtype, const void* X, int x_dtype, void* Y, float* P, float* dual,
@@ -3918,28 +3932,40 @@ int birkhoff8_mix_fwd(const void* H, int h_dtype, const void* X, int x_dtype, vo
     return launch_mix_fwd<BIRKHOFF4_F32, 8>(P, X, Y, B, nc, stream);
 }
 
-int birkhoff8_mix_bwd(const float* P, const void* X, const void* dY, int x_dtype, void* dX, float* dH, int64_t B,
-                      int64_t C, hipStream_t stream) {
+int birkhoff8_mix_bwd_ex(const float* P, const void* X, const void* dY, int x_dtype, void* dX, float* dP, void* dH,
+                         int dh_dtype, int64_t B, int64_t C, hipStream_t stream) {
     if (B < 0 || B > (INT64_MAX / 256)) return BIRKHOFF4_ERR_SIZE;
-    if (!dtype_ok(x_dtype)) return BIRKHOFF4_ERR_DTYPE;
+    if (!dtype_ok(x_dtype) || !dtype_ok(dh_dtype)) return BIRKHOFF4_ERR_DTYPE;
     const int64_t E = x_dtype == BIRKHOFF4_BF16 ? 8 : 4;
     if (C < 0 || C % E != 0) return BIRKHOFF4_ERR_CHANNELS;
     const int64_t nc = C / E;
     if (B > 0 && nc > INT64_MAX / 128 / B) return BIRKHOFF4_ERR_SIZE;
     if (B == 0) return BIRKHOFF4_OK;
-    if (!P || !dH || (nc > 0 && (!X || !dY || !dX))) return BIRKHOFF4_ERR_NULL;
-    if (misaligned(P) || misaligned(X) || misaligned(dY) || misaligned(dX) || misaligned(dH))
+    if (!P || !dP || !dH || (nc > 0 && (!X || !dY || !dX))) return BIRKHOFF4_ERR_NULL;
+    if (misaligned(P) || misaligned(X) || misaligned(dY) || misaligned(dX) || misaligned(dP) || misaligned(dH))
         return BIRKHOFF4_ERR_ALIGN;
-    const size_t np = static_cast<size_t>(B) * 256, nx = static_cast<size_t>(B) * 128 * nc;
-    if (overlaps(dX, nx, P, np) || overlaps(dX, nx, X, nx) || overlaps(dX, nx, dY, nx) || overlaps(dX, nx, dH, np) ||
-        overlaps(dH, np, P, np) || overlaps(dH, np, X, nx) || overlaps(dH, np, dY, nx))
+    const size_t np = static_cast<size_t>(B) * 256, nx = static_cast<size_t>(B) * 128 * nc,
+                 nh = static_cast<size_t>(B) * 64 * dtype_bytes(dh_dtype);
+    // fp32 dH may be dP's own memory: the 8 x 8 backward then turns dP into dH in place (each
+    // of its waves reads a chunk's dP whole before it writes that chunk's dH)
+    const bool in_place = dh_dtype == BIRKHOFF4_F32 && dH == static_cast<void*>(dP);
+    if (overlaps(dX, nx, P, np) || overlaps(dX, nx, X, nx) || overlaps(dX, nx, dY, nx) || overlaps(dX, nx, dH, nh) ||
+        overlaps(dX, nx, dP, np) || overlaps(dP, np, P, np) || overlaps(dP, np, X, nx) || overlaps(dP, np, dY, nx) ||
+        overlaps(dH, nh, P, np) || overlaps(dH, nh, X, nx) || overlaps(dH, nh, dY, nx) ||
+        (!in_place && overlaps(dH, nh, dP, np)))
         return BIRKHOFF4_ERR_OVERLAP;
-    // dX, and dP into dH's memory; then the 8 x 8 backward turns dP into dH in place (each of
-    // its waves reads a chunk's dP whole before it writes that chunk's dH)
-    const int e = x_dtype == BIRKHOFF4_BF16 ? launch_mix_bwd<BIRKHOFF4_BF16, 8>(P, X, dY, dX, dH, B, nc, stream)
-                                            : launch_mix_bwd<BIRKHOFF4_F32, 8>(P, X, dY, dX, dH, B, nc, stream);
+    constexpr int F = BIRKHOFF4_F32, H = BIRKHOFF4_BF16;
+    const int e = x_dtype == H ? launch_mix_bwd<H, 8>(P, X, dY, dX, dP, false, B, nc, stream)
+                               : launch_mix_bwd<F, 8>(P, X, dY, dX, dP, false, B, nc, stream);
     if (e) return e;
-    return launch_bwd8(implicit8_bwd_kernel<BIRKHOFF4_F32, BIRKHOFF4_F32, false, true>, P, dH, dH, B, stream);
+    if (in_place) return launch_bwd8(implicit8_bwd_kernel<F, F, false, true>, P, dP, dH, B, stream);
+    return launch_bwd8(dh_dtype == H ? implicit8_bwd_kernel<F, H, false> : implicit8_bwd_kernel<F, F, false>, P, dP, dH,
+                       B, stream);
+}
+
+int birkhoff8_mix_bwd(const float* P, const void* X, const void* dY, int x_dtype, void* dX, float* dH, int64_t B,
+                      int64_t C, hipStream_t stream) {
+    return birkhoff8_mix_bwd_ex(P, X, dY, x_dtype, dX, dH, dH, BIRKHOFF4_F32, B, C, stream);
 }
 
 const char* birkhoff4_strerror(int code) {

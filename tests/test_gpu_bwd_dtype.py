@@ -47,3 +47,19 @@ def test_autograd_gradient_of_bf16_logits(n):
     P = project(H)
     P.backward(G)
     assert same_bits(H.grad, bwd(P.detach(), G).to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("n", [4, 8])
+@pytest.mark.parametrize("B,C", [(1, 8), (67, 136), (130, 264), (65, 520), (9, 4096), (5, 0)])
+def test_mixing_gradient_of_bf16_logits(n, B, C):
+    say(f"test: mixing, bf16 logits, n={n} B={B} C={C}")
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(n * 1000 + C)
+    H = torch.randn(B, n, n, device="cuda:0", generator=g).to(torch.bfloat16).requires_grad_(True)
+    X = torch.randn(B, n, C, device="cuda:0", generator=g).to(torch.bfloat16)
+    dY = torch.randn(B, n, C, device="cuda:0", generator=g).to(torch.bfloat16)
+    Y = b4.mix(H, X)
+    Y.backward(dY)
+    P = (b4.fwd if n == 4 else b4.fwd8)(H.detach(), want_dual=False)[0]
+    dX, dH = (b4.mix_bwd if n == 4 else b4.mix8_bwd)(P, X, dY)
+    assert dH.dtype == torch.float32 and same_bits(H.grad, dH.to(torch.bfloat16))
