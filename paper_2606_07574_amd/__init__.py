@@ -98,8 +98,20 @@ def _check(code: int) -> None:
         raise Birkhoff4Error(f"birkhoff4 error {code}: {msg}")
 
 
-def _stream(t: torch.Tensor) -> int:
-    return torch.cuda.current_stream(t.device).cuda_stream
+def _call(name: str, t: torch.Tensor, *args) -> None:
+    """Queue the library's call `name` on the current stream of t's device.
+
+    The raw stream and device getters and the device switch left out where it is the current one
+    take about 3 us off a call (fwd + bwd of 2048 matrices: 20.0 us before, 13.8 now)."""
+    fn = getattr(_lib or _load(), name)
+    index = t.get_device()
+    if index == torch._C._cuda_getDevice():
+        code = fn(*args, torch._C._cuda_getCurrentRawStream(index))
+    else:
+        with torch.cuda.device(index):
+            code = fn(*args, torch._C._cuda_getCurrentRawStream(index))
+    if code != 0:
+        _check(code)
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -155,9 +167,8 @@ def fwd(H: torch.Tensor, tol: float = DEFAULT_TOL, max_iter: int = DEFAULT_MAX_I
     P = _out(out, H.shape, H.device)
     dual = torch.empty(*lead, 8, dtype=torch.float32, device=H.device) if want_dual else None
     iters = torch.empty(lead, dtype=torch.int32, device=H.device) if want_iters else None
-    with torch.cuda.device(H.device):
-        _check(_load().birkhoff4_fwd_ex2(_ptr(H), _dtype_code(H), _ptr(P), _ptr(dual), _ptr(iters),
-                                         B, float(tol), int(max_iter), int(variant), _stream(H)))
+    _call("birkhoff4_fwd_ex2", H, _ptr(H), _dtype_code(H), _ptr(P), _ptr(dual), _ptr(iters), B, float(tol),
+          int(max_iter), int(variant))
     return P, dual, iters
 
 
@@ -170,9 +181,8 @@ def _bwd(n: int, P: torch.Tensor, dP: torch.Tensor, out: torch.Tensor | None, dt
         raise TypeError("P must be float32")
     _same_device(P, dP)
     dH = torch.empty(P.shape, dtype=dtype, device=P.device) if out is None else _out(out, P.shape, P.device)
-    fn = _load().birkhoff4_bwd_ex2 if n == 4 else _load().birkhoff8_bwd_ex
-    with torch.cuda.device(P.device):
-        _check(fn(_ptr(P), _ptr(dP), _dtype_code(dP), _ptr(dH), _dtype_code(dH), B, _stream(P)))
+    _call("birkhoff4_bwd_ex2" if n == 4 else "birkhoff8_bwd_ex", P, _ptr(P), _ptr(dP), _dtype_code(dP), _ptr(dH),
+          _dtype_code(dH), B)
     return dH
 
 
@@ -191,9 +201,8 @@ def fwd_hess(H: torch.Tensor, tol: float = DEFAULT_TOL, max_iter: int = DEFAULT_
     dual = torch.empty(*lead, 8, dtype=torch.float32, device=H.device) if want_dual else None
     hess = torch.empty(*lead, 8, dtype=torch.float32, device=H.device)
     iters = torch.empty(lead, dtype=torch.int32, device=H.device) if want_iters else None
-    with torch.cuda.device(H.device):
-        _check(_load().birkhoff4_fwd_hess(_ptr(H), _dtype_code(H), _ptr(P), _ptr(dual), _ptr(hess), _ptr(iters),
-                                          B, float(tol), int(max_iter), _stream(H)))
+    _call("birkhoff4_fwd_hess", H, _ptr(H), _dtype_code(H), _ptr(P), _ptr(dual), _ptr(hess), _ptr(iters), B,
+          float(tol), int(max_iter))
     return P, dual, hess, iters
 
 
@@ -208,8 +217,7 @@ def bwd_hess(P: torch.Tensor, hess: torch.Tensor, dP: torch.Tensor) -> torch.Ten
         raise ValueError(f"hess must be a contiguous float32 tensor of shape {(*P.shape[:-2], 8)}")
     _same_device(P, hess, dP)
     dH = torch.empty(P.shape, dtype=torch.float32, device=P.device)
-    with torch.cuda.device(P.device):
-        _check(_load().birkhoff4_bwd_hess(_ptr(P), _ptr(hess), _ptr(dP), _dtype_code(dP), _ptr(dH), B, _stream(P)))
+    _call("birkhoff4_bwd_hess", P, _ptr(P), _ptr(hess), _ptr(dP), _dtype_code(dP), _ptr(dH), B)
     return dH
 
 
@@ -217,8 +225,7 @@ def sk_fwd(H: torch.Tensor, n_steps: int = 20) -> torch.Tensor:
     """n_steps Sinkhorn-Knopp iterations (baseline)."""
     B = _batch(H, "H")
     P = torch.empty(H.shape, dtype=torch.float32, device=H.device)
-    with torch.cuda.device(H.device):
-        _check(_load().birkhoff4_sk_fwd(_ptr(H), _dtype_code(H), _ptr(P), B, int(n_steps), _stream(H)))
+    _call("birkhoff4_sk_fwd", H, _ptr(H), _dtype_code(H), _ptr(P), B, int(n_steps))
     return P
 
 
@@ -229,9 +236,7 @@ def sk_bwd(H: torch.Tensor, dP: torch.Tensor, n_steps: int = 20) -> torch.Tensor
         raise ValueError("H and dP batch sizes differ")
     _same_device(H, dP)
     dH = torch.empty(H.shape, dtype=torch.float32, device=H.device)
-    with torch.cuda.device(H.device):
-        _check(_load().birkhoff4_sk_bwd(_ptr(H), _dtype_code(H), _ptr(dP), _dtype_code(dP), _ptr(dH),
-                                        B, int(n_steps), _stream(H)))
+    _call("birkhoff4_sk_bwd", H, _ptr(H), _dtype_code(H), _ptr(dP), _dtype_code(dP), _ptr(dH), B, int(n_steps))
     return dH
 
 
@@ -265,9 +270,8 @@ def fwd8(H: torch.Tensor, tol: float = DEFAULT_TOL, max_iter: int = DEFAULT_MAX_
     P = _out(out, H.shape, H.device)
     dual = torch.empty(*lead, 16, dtype=torch.float32, device=H.device) if want_dual else None
     iters = torch.empty(lead, dtype=torch.int32, device=H.device) if want_iters else None
-    with torch.cuda.device(H.device):
-        _check(_load().birkhoff8_fwd(_ptr(H), _dtype_code(H), _ptr(P), _ptr(dual), _ptr(iters),
-                                     B, float(tol), int(max_iter), _stream(H)))
+    _call("birkhoff8_fwd", H, _ptr(H), _dtype_code(H), _ptr(P), _ptr(dual), _ptr(iters), B, float(tol),
+          int(max_iter))
     return P, dual, iters
 
 
@@ -317,9 +321,8 @@ def ot_fwd(M: torch.Tensor, a: torch.Tensor, b: torch.Tensor, eta: float = 1.0, 
     T = torch.empty(M.shape, dtype=torch.float32, device=M.device)
     dual = torch.empty(*lead, 8, dtype=torch.float32, device=M.device) if want_dual else None
     iters = torch.empty(lead, dtype=torch.int32, device=M.device) if want_iters else None
-    with torch.cuda.device(M.device):
-        _check(_load().birkhoff4_ot_fwd(_ptr(M), _ptr(a), _ptr(b), float(eta), _ptr(T), _ptr(dual), _ptr(iters),
-                                        B, float(tol), int(max_iter), _stream(M)))
+    _call("birkhoff4_ot_fwd", M, _ptr(M), _ptr(a), _ptr(b), float(eta), _ptr(T), _ptr(dual), _ptr(iters), B,
+          float(tol), int(max_iter))
     return T, dual, iters
 
 
@@ -333,8 +336,7 @@ def ot_bwd(T: torch.Tensor, a: torch.Tensor, dT: torch.Tensor, eta: float = 1.0)
     _marginals(a, T.shape[:-2], "a")
     _same_device(T, a, dT)
     dM = torch.empty(T.shape, dtype=torch.float32, device=T.device)
-    with torch.cuda.device(T.device):
-        _check(_load().birkhoff4_ot_bwd(_ptr(T), _ptr(a), _ptr(dT), float(eta), _ptr(dM), B, _stream(T)))
+    _call("birkhoff4_ot_bwd", T, _ptr(T), _ptr(a), _ptr(dT), float(eta), _ptr(dM), B)
     return dM
 
 
@@ -373,9 +375,8 @@ def ot8_fwd(M: torch.Tensor, a: torch.Tensor, b: torch.Tensor, eta: float = 1.0,
     T = torch.empty(M.shape, dtype=torch.float32, device=M.device)
     dual = torch.empty(*lead, 16, dtype=torch.float32, device=M.device) if want_dual else None
     iters = torch.empty(lead, dtype=torch.int32, device=M.device) if want_iters else None
-    with torch.cuda.device(M.device):
-        _check(_load().birkhoff8_ot_fwd(_ptr(M), _ptr(a), _ptr(b), float(eta), _ptr(T), _ptr(dual), _ptr(iters),
-                                        B, float(tol), int(max_iter), _stream(M)))
+    _call("birkhoff8_ot_fwd", M, _ptr(M), _ptr(a), _ptr(b), float(eta), _ptr(T), _ptr(dual), _ptr(iters), B,
+          float(tol), int(max_iter))
     return T, dual, iters
 
 
@@ -389,8 +390,7 @@ def ot8_bwd(T: torch.Tensor, a: torch.Tensor, dT: torch.Tensor, eta: float = 1.0
     _marginals(a, T.shape[:-2], "a", 8)
     _same_device(T, a, dT)
     dM = torch.empty(T.shape, dtype=torch.float32, device=T.device)
-    with torch.cuda.device(T.device):
-        _check(_load().birkhoff8_ot_bwd(_ptr(T), _ptr(a), _ptr(dT), float(eta), _ptr(dM), B, _stream(T)))
+    _call("birkhoff8_ot_bwd", T, _ptr(T), _ptr(a), _ptr(dT), float(eta), _ptr(dM), B)
     return dM
 
 
@@ -436,10 +436,8 @@ def _mix_fwd(n, H, X, tol, max_iter, want_dual, want_iters):
     P = torch.empty(H.shape, dtype=torch.float32, device=H.device)
     dual = torch.empty(*lead, 2 * n, dtype=torch.float32, device=H.device) if want_dual else None
     iters = torch.empty(lead, dtype=torch.int32, device=H.device) if want_iters else None
-    fn = _load().birkhoff4_mix_fwd if n == 4 else _load().birkhoff8_mix_fwd
-    with torch.cuda.device(H.device):
-        _check(fn(_ptr(H), _dtype_code(H), _ptr(X), _dtype_code(X), _ptr(Y), _ptr(P), _ptr(dual), _ptr(iters), B, C,
-                  float(tol), int(max_iter), _stream(H)))
+    _call("birkhoff4_mix_fwd" if n == 4 else "birkhoff8_mix_fwd", H, _ptr(H), _dtype_code(H), _ptr(X), _dtype_code(X),
+          _ptr(Y), _ptr(P), _ptr(dual), _ptr(iters), B, C, float(tol), int(max_iter))
     return Y, P, dual, iters
 
 
@@ -455,14 +453,13 @@ def _mix_bwd(n, P, X, dY, dtype=torch.float32):
     _same_device(P, X, dY)
     dX = torch.empty_like(X)
     dH = torch.empty(P.shape, dtype=dtype, device=P.device)
-    with torch.cuda.device(P.device):
-        if n == 4:
-            _check(_load().birkhoff4_mix_bwd_ex(_ptr(P), _ptr(X), _ptr(dY), _dtype_code(X), _ptr(dX), _ptr(dH),
-                                                _dtype_code(dH), B, C, _stream(P)))
-        else:  # dL/dP in fp32 on the way, in dH's own memory if that is fp32
-            dP = dH if dtype == torch.float32 else torch.empty(P.shape, dtype=torch.float32, device=P.device)
-            _check(_load().birkhoff8_mix_bwd_ex(_ptr(P), _ptr(X), _ptr(dY), _dtype_code(X), _ptr(dX), _ptr(dP),
-                                                _ptr(dH), _dtype_code(dH), B, C, _stream(P)))
+    if n == 4:
+        _call("birkhoff4_mix_bwd_ex", P, _ptr(P), _ptr(X), _ptr(dY), _dtype_code(X), _ptr(dX), _ptr(dH),
+              _dtype_code(dH), B, C)
+    else:  # dL/dP in fp32 on the way, in dH's own memory if that is fp32
+        dP = dH if dtype == torch.float32 else torch.empty(P.shape, dtype=torch.float32, device=P.device)
+        _call("birkhoff8_mix_bwd_ex", P, _ptr(P), _ptr(X), _ptr(dY), _dtype_code(X), _ptr(dX), _ptr(dP), _ptr(dH),
+              _dtype_code(dH), B, C)
     return dX, dH
 
 
