@@ -80,7 +80,7 @@ constexpr float kTiny = 1e-30f;
 // factors of T that are far below fp32 resolution anyway.
 constexpr float kPivMin = 1e-30f;
 constexpr float kFltMin = 1.17549435e-38f;
-constexpr int kMaxSkSteps = 48;   // sk_bwd keeps (n+1) x 4 floats per lane in LDS
+constexpr int kMaxSkSteps = 48;   // sk_bwd keeps 2 n floats per lane in LDS
 constexpr int kSkRegSteps = 20;   // step count whose backward keeps the iterates in VGPRs
 constexpr int kMaxIterCap = 10000;
 // Batches up to this size take the four-lanes-per-problem forward by default.
@@ -1475,43 +1475,109 @@ __global__ __launch_bounds__(kMixShortBlock) void mix_bwd_short_kernel(const flo
 }
 
 // ---------------------------------------------------------------------------
-// Sinkhorn-Knopp baseline (eq. sinkhorn_knopp), one problem per lane
+// Sinkhorn-Knopp baseline (eq. sinkhorn_knopp), mostly four lanes per problem
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void sk_kernel_matrix(const float h[16], float A[16]) {
+// Lane q of a quad holds row q and column q of A, u_q and v_q. A half-step is a dot product
+// with the other vector, whose entries the multiply-adds read from the quad's lanes (DPP
+// operands), so the four lanes share the work of a problem without repeating any of it, an
+// iterate costs one register, and loads and stores are whole rows. Bound: VALU issue.
+
+// sum_j a_j x_j with x_j held by lane j of the quad: a_3 x_3 first, then fused multiply-adds.
+// Written as instructions because the compiler moves each x_j into a register of its own
+// before it multiplies. s_nop 1: a DPP operand may be read two wait states after its write.
+#define QUAD_PERM(j) " quad_perm:[" #j "," #j "," #j "," #j "] row_mask:0xf bank_mask:0xf\n\t"
+__device__ __forceinline__ float qdot(const float a[4], float x) {
+    float r;
+    asm("s_nop 1\n\t"
+        "v_mul_f32_dpp %0, %1, %5" QUAD_PERM(3)
+        "v_fmac_f32_dpp %0, %1, %4" QUAD_PERM(2)
+        "v_fmac_f32_dpp %0, %1, %3" QUAD_PERM(1)
+        "v_fmac_f32_dpp %0, %1, %2" QUAD_PERM(0)
+        : "=&v"(r) : "v"(x), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]));
+    return r;
+}
+
+// c_j += s x_j with x_j held by lane j of the quad.
+__device__ __forceinline__ void qaxpy(float c[4], float s, float x) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %4, %5" QUAD_PERM(0)
+        "v_fmac_f32_dpp %1, %4, %5" QUAD_PERM(1)
+        "v_fmac_f32_dpp %2, %4, %5" QUAD_PERM(2)
+        "v_fmac_f32_dpp %3, %4, %5" QUAD_PERM(3)
+        : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]) : "v"(x), "v"(s));
+}
+#undef QUAD_PERM
+
+// 1 / max(den, FLT_MIN): an underflowed denominator stays finite, at exactly 2^126. (An
+// instruction too: the compiler would first canonicalise what qdot returns.)
+__device__ __forceinline__ float sk_rcp(float den) {
+    asm("v_max_f32_e32 %0, 0x800000, %0" : "+v"(den));
+    return rcp(den);
+}
+constexpr float kSkClamped = 1.f / kFltMin;
+
+// Row q of A = exp(H - row max) from row q of H, and column q gathered from the quad.
+__device__ __forceinline__ void sk_matrix(const float h[4], int q, float A[4], float Ac[4]) {
+    const float m = __builtin_fmaxf(__builtin_fmaxf(h[0], h[1]), __builtin_fmaxf(h[2], h[3]));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float m = __builtin_fmaxf(__builtin_fmaxf(h[4 * i], h[4 * i + 1]),
-                                        __builtin_fmaxf(h[4 * i + 2], h[4 * i + 3]));
-#pragma unroll
-        for (int j = 0; j < 4; ++j) A[4 * i + j] = ex2((h[4 * i + j] - m) * kLog2e);
+    for (int j = 0; j < 4; ++j) A[j] = ex2((h[j] - m) * kLog2e);
+    auto pick = [q](float x0, float x1, float x2, float x3) { return q == 0 ? x0 : q == 1 ? x1 : q == 2 ? x2 : x3; };
+    Ac[0] = pick(qget<0>(A[0]), qget<0>(A[1]), qget<0>(A[2]), qget<0>(A[3]));
+    Ac[1] = pick(qget<1>(A[0]), qget<1>(A[1]), qget<1>(A[2]), qget<1>(A[3]));
+    Ac[2] = pick(qget<2>(A[0]), qget<2>(A[1]), qget<2>(A[2]), qget<2>(A[3]));
+    Ac[3] = pick(qget<3>(A[0]), qget<3>(A[1]), qget<3>(A[2]), qget<3>(A[3]));
+}
+
+constexpr int kSkBlock = 256;  // 64 problems
+
+template <int DT>
+__global__ __launch_bounds__(kSkBlock) void sk_fwd_kernel(const void* __restrict__ H, float* __restrict__ P,
+                                                          int64_t B, int n_steps) {
+    const int q = threadIdx.x & 3;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * (kSkBlock / 4);
+    for (int64_t b = static_cast<int64_t>(blockIdx.x) * (kSkBlock / 4) + (threadIdx.x >> 2); b < B; b += stride) {
+        float h[4], A[4], Ac[4], u = 0.f, v = 1.f;
+        load_row<DT>(H, b, q, h);
+        sk_matrix(h, q, A, Ac);
+        for (int k = 0; k < n_steps; ++k) {
+            u = sk_rcp(qdot(A, v));
+            v = sk_rcp(qdot(Ac, u));
+        }
+        reinterpret_cast<v4f*>(P)[4 * b + q] = v4f{u * A[0] * qget<0>(v), u * A[1] * qget<1>(v), u * A[2] * qget<2>(v),
+                                                   u * A[3] * qget<3>(v)};
     }
 }
 
-// u = 1 / max(A v, FLT_MIN), v = 1 / max(A^T u, FLT_MIN)
-__device__ __forceinline__ void sk_u(const float A[16], const float v[4], float u[4]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        u[i] = rcp(__builtin_fmaxf(__builtin_fmaf(A[4 * i], v[0], __builtin_fmaf(A[4 * i + 1], v[1],
-                   __builtin_fmaf(A[4 * i + 2], v[2], A[4 * i + 3] * v[3]))), kFltMin));
-}
-__device__ __forceinline__ void sk_v(const float A[16], const float u[4], float v[4]) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        v[j] = rcp(__builtin_fmaxf(__builtin_fmaf(A[j], u[0], __builtin_fmaf(A[4 + j], u[1],
-                   __builtin_fmaf(A[8 + j], u[2], A[12 + j] * u[3]))), kFltMin));
-}
+// One problem per lane: where the steps of a large batch outweigh its loads and stores this
+// has a little less to issue than the quads (no wait states). 2^20 problems fp32, this / quads in
+// us: 10 steps 32.0 / 24.0, 20 steps 36.8 / 38.9, 30 steps 49.1 / 54.8; 2 * 10^5: 20 steps 11.7 /
+// 10.6; 5000: 20 steps 4.7 / 3.1.
+constexpr int64_t kSkLaneMinB = int64_t(1) << 19;
+constexpr int kSkLaneMinSteps = 16;
 
 template <int DT>
-__global__ __launch_bounds__(256) void sk_fwd_kernel(const void* __restrict__ H, float* __restrict__ P,
-                                                      int64_t B, int n_steps) {
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    for (int64_t b = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; b < B; b += stride) {
+__global__ __launch_bounds__(kSkBlock) void sk_fwd_lane_kernel(const void* __restrict__ H, float* __restrict__ P,
+                                                               int64_t B, int n_steps) {
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kSkBlock;
+    for (int64_t b = static_cast<int64_t>(blockIdx.x) * kSkBlock + threadIdx.x; b < B; b += stride) {
         float h[16], A[16], u[4], v[4] = {1.f, 1.f, 1.f, 1.f};
         load16<DT>(H, b, h);
-        sk_kernel_matrix(h, A);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float m = __builtin_fmaxf(__builtin_fmaxf(h[4 * i], h[4 * i + 1]),
+                                            __builtin_fmaxf(h[4 * i + 2], h[4 * i + 3]));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) A[4 * i + j] = ex2((h[4 * i + j] - m) * kLog2e);
+        }
         for (int k = 0; k < n_steps; ++k) {
-            sk_u(A, v, u);
-            sk_v(A, u, v);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                u[i] = rcp(__builtin_fmaxf(__builtin_fmaf(A[4 * i], v[0], __builtin_fmaf(A[4 * i + 1], v[1],
+                           __builtin_fmaf(A[4 * i + 2], v[2], A[4 * i + 3] * v[3]))), kFltMin));
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                v[j] = rcp(__builtin_fmaxf(__builtin_fmaf(A[j], u[0], __builtin_fmaf(A[4 + j], u[1],
+                           __builtin_fmaf(A[8 + j], u[2], A[12 + j] * u[3]))), kFltMin));
         }
         float out[16];
 #pragma unroll
@@ -1522,144 +1588,102 @@ __global__ __launch_bounds__(256) void sk_fwd_kernel(const void* __restrict__ H,
     }
 }
 
-// Adjoints of P = diag(u) A diag(v) for dL/dP = G: A-bar = G o u v^T, u-bar, v-bar.
-__device__ __forceinline__ void sk_adjoint_init(const float A[16], const float G[16], const float u[4],
-                                                const float v[4], float Ab[16], float ub[4], float vb[4]) {
+// Reverse mode through the steps. State of the reverse sweep: lane q's row of A-bar and the
+// adjoints of u_q and v_q.
+struct SkAdjoint {
+    float Ab[4], ub, vb;
+};
+
+// Adjoints of P = diag(u) A diag(v) for dL/dP = G (row q).
+__device__ __forceinline__ SkAdjoint sk_adjoint_init(const float A[4], const float G[4], float u, float v, int q) {
+    SkAdjoint d;
+    const float vj[4] = {qget<0>(v), qget<1>(v), qget<2>(v), qget<3>(v)};
+    float w[4];
+    d.ub = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ub[i] = 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) vb[j] = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float gg = G[4 * i + j];
-            Ab[4 * i + j] = gg * u[i] * v[j];
-            ub[i] = __builtin_fmaf(gg * A[4 * i + j], v[j], ub[i]);
-            vb[j] = __builtin_fmaf(gg * u[i], A[4 * i + j], vb[j]);
-        }
+    for (int j = 0; j < 4; ++j) {
+        d.Ab[j] = G[j] * u * vj[j];
+        d.ub = __builtin_fmaf(G[j] * A[j], vj[j], d.ub);
+        w[j] = qsum(G[j] * u * A[j]);  // sum_i G_ij u_i A_ij
+    }
+    d.vb = q == 0 ? w[0] : q == 1 ? w[1] : q == 2 ? w[2] : w[3];
+    return d;
 }
 
 // One step back through u^(k) = 1 / max(A v^(k-1), FLT_MIN), v^(k) = 1 / max(A^T u^(k),
-// FLT_MIN): u^(k) is recomputed from v^(k-1); on entry vb holds dL/dv^(k) and ub the
-// direct part of dL/du^(k) (zero before the last step's), on exit vb holds dL/dv^(k-1),
-// ub is cleared and A-bar has gathered both steps' terms. A clamped denominator
-// contributes no gradient.
-__device__ __forceinline__ void sk_reverse(const float A[16], const float vk[4], const float vp[4], float Ab[16],
-                                           float ub[4], float vb[4]) {
-    float uk[4];
-    sk_u(A, vp, uk);
-    float bb[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float den = __builtin_fmaf(A[j], uk[0], __builtin_fmaf(A[4 + j], uk[1],
-                          __builtin_fmaf(A[8 + j], uk[2], A[12 + j] * uk[3])));
-        bb[j] = den >= kFltMin ? -vb[j] * vk[j] * vk[j] : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            ub[i] = __builtin_fmaf(A[4 * i + j], bb[j], ub[i]);
-            Ab[4 * i + j] = __builtin_fmaf(uk[i], bb[j], Ab[4 * i + j]);
-        }
-    float ab[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float den = __builtin_fmaf(A[4 * i], vp[0], __builtin_fmaf(A[4 * i + 1], vp[1],
-                          __builtin_fmaf(A[4 * i + 2], vp[2], A[4 * i + 3] * vp[3])));
-        ab[i] = den >= kFltMin ? -ub[i] * uk[i] * uk[i] : 0.f;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) vb[j] = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            vb[j] = __builtin_fmaf(A[4 * i + j], ab[i], vb[j]);
-            Ab[4 * i + j] = __builtin_fmaf(ab[i], vp[j], Ab[4 * i + j]);
-        }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) ub[i] = 0.f;
+// FLT_MIN): on entry vb holds dL/dv^(k) and, at the last step, ub the direct part of dL/du^(k);
+// on exit vb holds dL/dv^(k-1) and A-bar has gathered both steps' terms. A clamped denominator
+// (an iterate of 2^126) contributes no gradient.
+__device__ __forceinline__ void sk_reverse(const float A[4], const float Ac[4], float uk, float vk, float vp, bool last,
+                                           SkAdjoint& d) {
+    const float bb = vk < kSkClamped ? -d.vb * vk * vk : 0.f;
+    const float t = qdot(A, bb);
+    const float ub = last ? d.ub + t : t;
+    const float ab = uk < kSkClamped ? -ub * uk * uk : 0.f;
+    qaxpy(d.Ab, uk, bb);
+    qaxpy(d.Ab, ab, vp);
+    d.vb = qdot(Ac, ab);
 }
 
-// Reverse mode through the n-step map, any n: the iterates v^(k) are kept in LDS (one
-// 64-lane block, [k][component][lane] so that lanes hit distinct banks).
+__device__ __forceinline__ void sk_store(float* __restrict__ dH, int64_t b, int q, const SkAdjoint& d, const float A[4]) {
+    reinterpret_cast<v4f*>(dH)[4 * b + q] = v4f{d.Ab[0] * A[0], d.Ab[1] * A[1], d.Ab[2] * A[2], d.Ab[3] * A[3]};
+}
+
+// Any number of steps: the iterates are kept in LDS (blocks of one wave, [k][lane]).
+constexpr int kSkLdsBlock = 64;
+
 template <int DT, int DG>
-__global__ __launch_bounds__(64) void sk_bwd_kernel(const void* __restrict__ H,
-                                                     const void* __restrict__ dP,
-                                                     float* __restrict__ dH, int64_t B, int n_steps) {
-    extern __shared__ float vbuf[];  // [(n_steps + 1) * 4][64]
-    const int lane = threadIdx.x;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    for (int64_t b = static_cast<int64_t>(blockIdx.x) * blockDim.x + lane; b < B; b += stride) {
-        float h[16], G[16], A[16], u[4], v[4] = {1.f, 1.f, 1.f, 1.f};
-        load16<DT>(H, b, h);
-        load16<DG>(dP, b, G);
-        sk_kernel_matrix(h, A);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) vbuf[j * 64 + lane] = 1.f;
+__global__ __launch_bounds__(kSkLdsBlock) void sk_bwd_kernel(const void* __restrict__ H, const void* __restrict__ dP,
+                                                             float* __restrict__ dH, int64_t B, int n_steps) {
+    extern __shared__ float iter[];  // u^(k) at [2 k - 2][64], v^(k) at [2 k - 1][64]
+    const int lane = threadIdx.x, q = lane & 3;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * (kSkLdsBlock / 4);
+    for (int64_t b = static_cast<int64_t>(blockIdx.x) * (kSkLdsBlock / 4) + (lane >> 2); b < B; b += stride) {
+        float h[4], G[4], A[4], Ac[4], u = 0.f, v = 1.f;
+        load_row<DT>(H, b, q, h);
+        load_row<DG>(dP, b, q, G);
+        sk_matrix(h, q, A, Ac);
         for (int k = 1; k <= n_steps; ++k) {
-            sk_u(A, v, u);
-            sk_v(A, u, v);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) vbuf[(4 * k + j) * 64 + lane] = v[j];
+            u = sk_rcp(qdot(A, v));
+            v = sk_rcp(qdot(Ac, u));
+            iter[(2 * k - 2) * kSkLdsBlock + lane] = u;
+            iter[(2 * k - 1) * kSkLdsBlock + lane] = v;
         }
-        float Ab[16], ub[4], vb[4];
-        sk_adjoint_init(A, G, u, v, Ab, ub, vb);
+        SkAdjoint d = sk_adjoint_init(A, G, u, v, q);
         for (int k = n_steps; k >= 1; --k) {
-            float vk[4], vp[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                vk[j] = vbuf[(4 * k + j) * 64 + lane];
-                vp[j] = vbuf[(4 * (k - 1) + j) * 64 + lane];
-            }
-            sk_reverse(A, vk, vp, Ab, ub, vb);
+            const float vp = k > 1 ? iter[(2 * k - 3) * kSkLdsBlock + lane] : 1.f;
+            sk_reverse(A, Ac, u, v, vp, k == n_steps, d);
+            v = vp;
+            if (k > 1) u = iter[(2 * k - 4) * kSkLdsBlock + lane];
         }
-        float out[16];
-#pragma unroll
-        for (int q = 0; q < 16; ++q) out[q] = Ab[q] * A[q];
-        store16(dH, b, out);
+        sk_store(dH, b, q, d, A);
     }
 }
 
-// The same for a step count fixed at compile time: the iterates stay in VGPRs (the
-// loops are unrolled), so occupancy is set by registers, not by the LDS the iterates
-// would take. Same arithmetic in the same order as the LDS kernel.
+// The same for a step count fixed at compile time: the iterates stay in VGPRs. Same
+// arithmetic in the same order as the LDS kernel. 2^20 problems, 20 steps: 91 us; with one
+// problem per lane, which has registers for the v^(k) only and recomputes each u^(k), 117 us
+// (5000 problems: 4.1 and 9.5 us).
 template <int DT, int DG, int NS>
-__global__ __launch_bounds__(256, 3) void sk_bwd_reg_kernel(const void* __restrict__ H,
-                                                          const void* __restrict__ dP,
-                                                          float* __restrict__ dH, int64_t B) {
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    for (int64_t b = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; b < B; b += stride) {
-        float h[16], G[16], A[16], u[4], vs[NS + 1][4];
-        load16<DT>(H, b, h);
-        sk_kernel_matrix(h, A);
+__global__ __launch_bounds__(kSkBlock) void sk_bwd_reg_kernel(const void* __restrict__ H, const void* __restrict__ dP,
+                                                              float* __restrict__ dH, int64_t B) {
+    const int q = threadIdx.x & 3;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * (kSkBlock / 4);
+    for (int64_t b = static_cast<int64_t>(blockIdx.x) * (kSkBlock / 4) + (threadIdx.x >> 2); b < B; b += stride) {
+        float h[4], G[4], A[4], Ac[4], us[NS], vs[NS + 1];
+        load_row<DT>(H, b, q, h);
+        load_row<DG>(dP, b, q, G);
+        sk_matrix(h, q, A, Ac);
+        vs[0] = 1.f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) vs[0][j] = 1.f;
-#pragma unroll
-        for (int k = 1; k <= NS; ++k) {
-            sk_u(A, vs[k - 1], u);
-            sk_v(A, u, vs[k]);
+        for (int k = 0; k < NS; ++k) {
+            us[k] = sk_rcp(qdot(A, vs[k]));
+            vs[k + 1] = sk_rcp(qdot(Ac, us[k]));
         }
-        load16<DG>(dP, b, G);  // needed from here on only
-        float Ab[16], ub[4], vb[4];
-        sk_adjoint_init(A, G, u, vs[NS], Ab, ub, vb);
-        // Each reverse step recomputes u^(k) from v^(k-1); tying the step's inputs to the
-        // adjoint it receives keeps that work in its own step (hoisted ahead, or shared with
-        // the forward steps, it would keep ~20 values per step live at once).
+        SkAdjoint d = sk_adjoint_init(A, G, us[NS - 1], vs[NS], q);
 #pragma unroll
-        for (int k = NS; k >= 1; --k) {
-            float vk[4] = {vs[k][0], vs[k][1], vs[k][2], vs[k][3]};
-            float vp[4] = {vs[k - 1][0], vs[k - 1][1], vs[k - 1][2], vs[k - 1][3]};
-            asm volatile("" : "+v"(vk[0]), "+v"(vk[1]), "+v"(vk[2]), "+v"(vk[3]), "+v"(vp[0]), "+v"(vp[1]),
-                              "+v"(vp[2]), "+v"(vp[3]) : "v"(vb[0]), "v"(vb[1]), "v"(vb[2]), "v"(vb[3]));
-            sk_reverse(A, vk, vp, Ab, ub, vb);
-        }
-        float out[16];
-#pragma unroll
-        for (int q = 0; q < 16; ++q) out[q] = Ab[q] * A[q];
-        store16(dH, b, out);
+        for (int k = NS - 1; k >= 0; --k) sk_reverse(A, Ac, us[k], vs[k + 1], vs[k], k == NS - 1, d);
+        sk_store(dH, b, q, d, A);
     }
 }
 
@@ -3468,6 +3492,8 @@ int launch_bwd8(Kernel kern, const float* P, const void* dP, void* dH, int64_t B
     return launch_status();
 }
 
+constexpr int kSkGridPerCu = 256;  // blocks per CU of the Sinkhorn kernels' grid; further problems loop
+
 // Residual mixing: block and grid. A row is `cols` columns of 64 chunks, one per wave, up to
 // `most` waves per block; more columns are spread evenly over shares of the row (forward) or
 // turns of the block's waves (backward). Measured lines (us, bf16 unless said):
@@ -3789,13 +3815,11 @@ int birkhoff4_sk_fwd(const void* H, int h_dtype, float* P, int64_t B, int n_step
         return BIRKHOFF4_ERR_OVERLAP;
     int cus = 0, dev = 0;
     if (int e = device_cus(stream, &cus, &dev)) return e;
-    const int64_t grid = grid_for(B, 256, cus, 64);
-    if (h_dtype == BIRKHOFF4_BF16)
-        launch_kernel(sk_fwd_kernel<BIRKHOFF4_BF16>, dim3(static_cast<unsigned>(grid)), dim3(256), 0,
-                           stream, H, P, B, n_steps);
-    else
-        launch_kernel(sk_fwd_kernel<BIRKHOFF4_F32>, dim3(static_cast<unsigned>(grid)), dim3(256), 0,
-                           stream, H, P, B, n_steps);
+    const bool h16 = h_dtype == BIRKHOFF4_BF16, lanes = B >= kSkLaneMinB && n_steps >= kSkLaneMinSteps;
+    const int64_t grid = lanes ? grid_for(B, kSkBlock, cus, 64) : grid_for(B, kSkBlock / 4, cus, kSkGridPerCu);
+    auto kern = lanes ? (h16 ? sk_fwd_lane_kernel<BIRKHOFF4_BF16> : sk_fwd_lane_kernel<BIRKHOFF4_F32>)
+                      : (h16 ? sk_fwd_kernel<BIRKHOFF4_BF16> : sk_fwd_kernel<BIRKHOFF4_F32>);
+    launch_kernel(kern, dim3(static_cast<unsigned>(grid)), dim3(kSkBlock), 0, stream, H, P, B, n_steps);
     return launch_status();
 }
 
@@ -3813,36 +3837,19 @@ int birkhoff4_sk_bwd(const void* H, int h_dtype, const void* dP, int dp_dtype, f
         return BIRKHOFF4_ERR_OVERLAP;
     int cus = 0, dev = 0;
     if (int e = device_cus(stream, &cus, &dev)) return e;
-    if (n_steps == kSkRegSteps) {
-        const int64_t grid = grid_for(B, 256, cus, 64);
-        const dim3 g(static_cast<unsigned>(grid)), blk(256);
-        if (h_dtype == BIRKHOFF4_BF16) {
-            if (dp_dtype == BIRKHOFF4_BF16)
-                launch_kernel((sk_bwd_reg_kernel<BIRKHOFF4_BF16, BIRKHOFF4_BF16, kSkRegSteps>), g, blk, 0, stream, H, dP, dH, B);
-            else
-                launch_kernel((sk_bwd_reg_kernel<BIRKHOFF4_BF16, BIRKHOFF4_F32, kSkRegSteps>), g, blk, 0, stream, H, dP, dH, B);
-        } else {
-            if (dp_dtype == BIRKHOFF4_BF16)
-                launch_kernel((sk_bwd_reg_kernel<BIRKHOFF4_F32, BIRKHOFF4_BF16, kSkRegSteps>), g, blk, 0, stream, H, dP, dH, B);
-            else
-                launch_kernel((sk_bwd_reg_kernel<BIRKHOFF4_F32, BIRKHOFF4_F32, kSkRegSteps>), g, blk, 0, stream, H, dP, dH, B);
-        }
+    constexpr int F = BIRKHOFF4_F32, X = BIRKHOFF4_BF16, N = kSkRegSteps;
+    const bool h16 = h_dtype == X, g16 = dp_dtype == X;
+    if (n_steps == N) {
+        auto kern = h16 ? (g16 ? sk_bwd_reg_kernel<X, X, N> : sk_bwd_reg_kernel<X, F, N>)
+                        : (g16 ? sk_bwd_reg_kernel<F, X, N> : sk_bwd_reg_kernel<F, F, N>);
+        launch_kernel(kern, dim3(static_cast<unsigned>(grid_for(B, kSkBlock / 4, cus, kSkGridPerCu))), dim3(kSkBlock), 0,
+                      stream, H, dP, dH, B);
         return launch_status();
     }
-    const int64_t grid = grid_for(B, 64, cus, 64);
-    const size_t lds = static_cast<size_t>(n_steps + 1) * 4 * 64 * sizeof(float);
-    const dim3 g(static_cast<unsigned>(grid)), blk(64);
-    if (h_dtype == BIRKHOFF4_BF16) {
-        if (dp_dtype == BIRKHOFF4_BF16)
-            launch_kernel((sk_bwd_kernel<BIRKHOFF4_BF16, BIRKHOFF4_BF16>), g, blk, lds, stream, H, dP, dH, B, n_steps);
-        else
-            launch_kernel((sk_bwd_kernel<BIRKHOFF4_BF16, BIRKHOFF4_F32>), g, blk, lds, stream, H, dP, dH, B, n_steps);
-    } else {
-        if (dp_dtype == BIRKHOFF4_BF16)
-            launch_kernel((sk_bwd_kernel<BIRKHOFF4_F32, BIRKHOFF4_BF16>), g, blk, lds, stream, H, dP, dH, B, n_steps);
-        else
-            launch_kernel((sk_bwd_kernel<BIRKHOFF4_F32, BIRKHOFF4_F32>), g, blk, lds, stream, H, dP, dH, B, n_steps);
-    }
+    auto kern = h16 ? (g16 ? sk_bwd_kernel<X, X> : sk_bwd_kernel<X, F>) : (g16 ? sk_bwd_kernel<F, X> : sk_bwd_kernel<F, F>);
+    const unsigned lds = static_cast<unsigned>(2 * n_steps * kSkLdsBlock * sizeof(float));
+    launch_kernel(kern, dim3(static_cast<unsigned>(grid_for(B, kSkLdsBlock / 4, cus, 4 * kSkGridPerCu))),
+                  dim3(kSkLdsBlock), lds, stream, H, dP, dH, B, n_steps);
     return launch_status();
 }
 

@@ -1,0 +1,53 @@
+"""Sinkhorn-Knopp kernels at the edges of their layouts: four lanes per problem, one problem per
+lane for many steps of a large batch, register and LDS backward, ragged batches; the fp64
+oracle's map and its reverse-mode gradient."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2606_07574_amd as b4
+import workloads
+from tests._gpu import bits_to_dev, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def check(H, dP, Hd, dPd, steps, label):
+    P, dH = b4.sk_fwd(Hd, steps), b4.sk_bwd(Hd, dPd, steps)
+    torch.cuda.synchronize()
+    n = H.shape[0]
+    Pr = oracle.sk_fwd(H.astype(np.float64), steps)
+    dHr = oracle.sk_bwd(H.astype(np.float64), dP.astype(np.float64), steps)
+    pe = np.abs(P[:n].cpu().numpy() - Pr).max()
+    he = (np.abs(dH[:n].cpu().numpy() - dHr).max(axis=(1, 2)) / np.maximum(1.0, np.abs(dHr).max(axis=(1, 2)))).max()
+    say(f"  [{label}] P err={pe:.2e} dH rel err={he:.2e}")
+    # each of the 2 n half-steps rounds four products, their sum and a reciprocal (1 ulp): the
+    # relative error of an entry of P stays below 2 n * 8 * 2^-24; the gradient takes each step
+    # twice
+    bound = 16 * steps * 2.0 ** -24
+    assert pe <= bound and he <= 4 * bound
+    return P, dH
+
+
+@pytest.mark.parametrize("B", [1, 3, 15, 16, 17, 63, 64, 65, 1001])
+@pytest.mark.parametrize("steps", [1, 2, 20, 33])
+def test_ragged(B, steps):
+    say(f"test: Sinkhorn layouts, B={B}, {steps} steps")
+    H, dP = workloads.gauss(B, 2.0, seed=B + steps)
+    check(H, dP, to_dev(H), to_dev(dP), steps, f"B={B} n={steps}")
+    Hb, Gb = workloads.bf16_bits(H), workloads.bf16_bits(dP)
+    check(workloads.bf16_to_f32(Hb), workloads.bf16_to_f32(Gb), bits_to_dev(Hb), bits_to_dev(Gb), steps, "bf16")
+
+
+@pytest.mark.parametrize("steps", [15, 16, 20])
+@pytest.mark.parametrize("B", [(1 << 19) - 1, 1 << 19, (1 << 19) + 77])
+def test_large(B, steps):
+    say(f"test: Sinkhorn layouts, B={B}, {steps} steps")
+    H, dP = workloads.gauss(5003, 3.0, seed=steps)
+    k = -(-B // 5003)
+    Hd, dPd = (torch.cat([to_dev(x)] * k)[:B].contiguous() for x in (H, dP))
+    P, dH = check(H, dP, Hd, dPd, steps, f"B={B} n={steps}")
+    for i in range(5003, B, 5003):  # every copy of the problems gives the same bits
+        m = min(5003, B - i)
+        assert torch.equal(P[i:i + m], P[:m]) and torch.equal(dH[i:i + m], dH[:m])
