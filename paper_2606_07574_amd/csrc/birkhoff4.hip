@@ -2818,10 +2818,12 @@ __global__ __launch_bounds__(kB8Block, 2) void implicit8_bwd_kernel(const float*
 constexpr int kOtBlock = 256;
 constexpr int kOtWaves = kOtBlock / 64;
 constexpr int kOtSlot = 8;  // v4f per ring slot
-#ifndef OT_RANGES
-#define OT_RANGES 16384
-#endif
-constexpr int64_t kOtRanges = OT_RANGES;  // wave ranges per launch
+// Wave ranges per launch: 4096 waves are resident, and a range should be long enough that the
+// lanes refill many times before it drains; past kOtManyB problems two ranges per slot even out
+// the waves. us at eta = 0.5 with 4096 / 8192 / 16384 ranges: 4 * 10^5 problems 38.8 / 39.2 /
+// 39.0, 2^20 68.4 / 70.6 / 77.3, 2 * 10^6 123.8 / 121.7 / 127.4, 2^22 241 / 232 / 236.
+constexpr int64_t kOtRanges = 4096;
+constexpr int64_t kOtManyB = 3 * (int64_t(1) << 19);
 
 __device__ __forceinline__ v4f load4(const float* base, int64_t b) { return reinterpret_cast<const v4f*>(base)[b]; }
 
@@ -3446,14 +3448,13 @@ int dispatch_ot8_fwd(const float* M, const float* a, const float* b, float eta, 
     return launch_fwd8<F, false, false, true>(M, T, dual, iters, B, tol, max_iter, stream, a, b, eta);
 }
 
-// General OT: one range of problems per wave, blocks scheduled by the hardware (its problems
-// take few trials and its ranges are small, so the strided batches of the n = 8 forward do
-// not pay here).
+// General OT: one range of problems per wave, blocks scheduled by the hardware.
 template <bool WD, bool WI>
 int launch_ot_fwd(const float* M, const float* a, const float* b, float eta, float* T, float* dual, int32_t* iters,
                   int64_t B, float tol, int max_iter, hipStream_t stream) {
     const int64_t waves_min = (B + kMaxGrid * kOtWaves - 1) / (kMaxGrid * kOtWaves);
-    int64_t per_wave = (B + kOtRanges - 1) / kOtRanges;
+    const int64_t ranges = B < kOtManyB ? kOtRanges : 2 * kOtRanges;
+    int64_t per_wave = (B + ranges - 1) / ranges;
     if (per_wave < 64) per_wave = 64;
     if (per_wave < waves_min) per_wave = waves_min;
     const int64_t waves = (B + per_wave - 1) / per_wave;
