@@ -726,26 +726,26 @@ __device__ __forceinline__ void load_row(const void* base, int64_t b, int q, flo
     }
 }
 
-template <int DT, bool WRITE_DUAL, bool WRITE_ITERS>
-__global__ __launch_bounds__(256) void newton_fwd_quad_kernel(const void* __restrict__ H,
-                                                               float* __restrict__ P,
-                                                               float* __restrict__ dual,
-                                                               int32_t* __restrict__ iters, int64_t B,
-                                                               float tol, int max_iter) {
-    const int64_t gt = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t b = gt >> 2;       // this quad's problem
-    const int q = threadIdx.x & 3;   // this lane's row
-    const bool valid = b < B;        // uniform across the quad
+// A quad's projected problem: row q of P, the row's log2 normaliser, the column potentials
+// (the same in the four lanes) and the status word.
+struct QuadProblem {
+    float T[4], a, b[3];
+    int status;
+};
+
+// The projection of the quad's problem from its rows (h: this lane's). Every lane of the wave
+// takes part; quads without a problem (valid false, the same over the quad) do no steps.
+__device__ __forceinline__ QuadProblem quad_project(const float h[4], bool valid, float tol, int max_iter) {
+    QuadProblem out;
     // Initial point (column centring), eq. tij_stable in the log domain, as in init_problem.
-    float h[4] = {0.f, 0.f, 0.f, 0.f};
-    if (valid) load_row<DT>(H, b, q, h);
     float cm[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) cm[j] = 0.25f * kLog2e * qsum(h[j]);
     const float hs = (cm[0] + cm[1]) + (cm[2] + cm[3]);
     const float poison = hs - hs;  // 0, or NaN for a non-finite input anywhere in the matrix
     float b0 = cm[3] - cm[0] + poison, b1 = cm[3] - cm[1] + poison, b2 = cm[3] - cm[2] + poison;
-    float T[4], a;
+    float(&T)[4] = out.T;
+    float& a = out.a;
     {
         const float u0 = __builtin_fmaf(h[0], kLog2e, b0), u1 = __builtin_fmaf(h[1], kLog2e, b1),
                     u2 = __builtin_fmaf(h[2], kLog2e, b2), u3 = __builtin_fmaf(h[3], kLog2e, poison);
@@ -770,7 +770,8 @@ __global__ __launch_bounds__(256) void newton_fwd_quad_kernel(const void* __rest
     float gmax = gmax_of(g);
     const bool nonfinite = __builtin_isnan(b0);
     bool active = valid && !(gmax <= tol) && !nonfinite && max_iter > 0;
-    int status = nonfinite ? BIRKHOFF4_NON_FINITE : (gmax <= tol ? 0 : BIRKHOFF4_NOT_CONVERGED);
+    int& status = out.status;
+    status = nonfinite ? BIRKHOFF4_NON_FINITE : (gmax <= tol ? 0 : BIRKHOFF4_NOT_CONVERGED);
     Weights Wa = weights();
     float ga0 = g[0], ga1 = g[1], ga2 = g[2];
     float lam = __builtin_fmaxf(kLM * gmax, kLMFloor);
@@ -845,18 +846,36 @@ __global__ __launch_bounds__(256) void newton_fwd_quad_kernel(const void* __rest
             }
         }
     }
-    // outputs: lane q writes row q of P; lanes 0 and 1 write the dual record; lane 0 the status
-    if (valid) {
-        reinterpret_cast<v4f*>(P)[4 * b + q] = v4f{T[0], T[1], T[2], T[3]};
-        const float al0 = qget<0>(a), al1 = qget<1>(a), al2 = qget<2>(a), al3 = qget<3>(a);
-        if constexpr (WRITE_DUAL) {
-            v4f* dp = reinterpret_cast<v4f*>(dual) + 2 * b;
-            if (q == 0) dp[0] = v4f{-al0 * kLn2, -al1 * kLn2, -al2 * kLn2, -al3 * kLn2};
-            if (q == 1) dp[1] = v4f{b0 * kLn2, b1 * kLn2, b2 * kLn2, b0 * 0.f};
-        }
-        if constexpr (WRITE_ITERS)
-            if (q == 0) iters[b] = status;
+    out.b[0] = b0; out.b[1] = b1; out.b[2] = b2;
+    return out;
+}
+
+// Lane q writes row q of P; lanes 0 and 1 the dual record; lane 0 the status.
+template <bool WRITE_DUAL, bool WRITE_ITERS>
+__device__ __forceinline__ void store_quad(float* __restrict__ P, float* __restrict__ dual, int32_t* __restrict__ iters,
+                                           int64_t b, int q, const QuadProblem& r) {
+    reinterpret_cast<v4f*>(P)[4 * b + q] = v4f{r.T[0], r.T[1], r.T[2], r.T[3]};
+    if constexpr (WRITE_DUAL) {
+        const float al0 = qget<0>(r.a), al1 = qget<1>(r.a), al2 = qget<2>(r.a), al3 = qget<3>(r.a);
+        v4f* dp = reinterpret_cast<v4f*>(dual) + 2 * b;
+        if (q == 0) dp[0] = v4f{-al0 * kLn2, -al1 * kLn2, -al2 * kLn2, -al3 * kLn2};
+        if (q == 1) dp[1] = v4f{r.b[0] * kLn2, r.b[1] * kLn2, r.b[2] * kLn2, r.b[0] * 0.f};
     }
+    if constexpr (WRITE_ITERS)
+        if (q == 0) iters[b] = r.status;
+}
+
+template <int DT, bool WRITE_DUAL, bool WRITE_ITERS>
+__global__ __launch_bounds__(256) void newton_fwd_quad_kernel(const void* __restrict__ H, float* __restrict__ P,
+                                                              float* __restrict__ dual, int32_t* __restrict__ iters,
+                                                              int64_t B, float tol, int max_iter) {
+    const int64_t b = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) >> 2;  // this quad's problem
+    const int q = threadIdx.x & 3;   // this lane's row
+    const bool valid = b < B;        // uniform across the quad
+    float h[4] = {0.f, 0.f, 0.f, 0.f};
+    if (valid) load_row<DT>(H, b, q, h);
+    const QuadProblem r = quad_project(h, valid, tol, max_iter);
+    if (valid) store_quad<WRITE_DUAL, WRITE_ITERS>(P, dual, iters, b, q, r);
 }
 
 // ---------------------------------------------------------------------------
@@ -2359,38 +2378,28 @@ __global__ __launch_bounds__(kB8Block, 2) void newton8_fwd_kernel(const void* __
 
 constexpr int kGrp8Block = 64;
 
-template <int R, int DT, bool WRITE_DUAL, bool WRITE_ITERS, bool OT>
-__global__ __launch_bounds__(kGrp8Block) void newton8_fwd_group_kernel(const void* __restrict__ H,
-                                                                       float* __restrict__ P, float* __restrict__ dual,
-                                                                       int32_t* __restrict__ iters, int64_t B,
-                                                                       float tol, int max_iter,
-                                                                       const float* __restrict__ av,
-                                                                       const float* __restrict__ bv, float eta) {
-    constexpr int G = 8 / R;                        // lanes per problem
-    const float hsc = OT ? -kLog2e / eta : kLog2e;  // log2-unit logits per unit of H (or of M)
-    const int64_t b = static_cast<int64_t>(blockIdx.x) * (kGrp8Block / G) + threadIdx.x / G;  // this group's problem
-    const int q = threadIdx.x % G;  // this lane's rows: R q .. R q + R - 1
-    const bool valid = b < B;       // uniform across the group
-    float h[R][8], ma[R], mb[8];    // logits; OT: these rows' masses and all column masses
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) h[r][j] = 0.f;
-        ma[r] = 1.f;
-        if (valid) {
-            load_row8<DT>(H, b, R * q + r, h[r]);
-            if constexpr (OT) ma[r] = av[8 * b + R * q + r];
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) mb[j] = 1.f;
+// A group's projected problem: this lane's rows of P (OT: of S), their log2 normalisers, the
+// column potentials (the same in all its lanes) and the status word.
+template <int R>
+struct GroupProblem {
+    float T[R][8], a[R], beta[7];
+    int status;
+};
+
+// The solution of the group's problem from this lane's rows h (log2-unit logits per unit hsc)
+// and, with OT, their masses ma and all column masses mb. Every lane of the wave takes part;
+// groups without a problem (valid false, the same over the group) do no steps.
+template <int R, bool OT>
+__device__ __forceinline__ GroupProblem<R> group_project8(const float h[R][8], const float ma[R], const float mb[8],
+                                                          float hsc, bool valid, float tol, int max_iter) {
+    constexpr int G = 8 / R;
+    GroupProblem<R> out;
+    auto& T = out.T;
+    auto& a = out.a;
+    auto& beta = out.beta;
+    int& status = out.status;
     bool fin = true;
     if constexpr (OT) {
-        if (valid) {
-            const v4f b0 = reinterpret_cast<const v4f*>(bv)[2 * b], b1 = reinterpret_cast<const v4f*>(bv)[2 * b + 1];
-            mb[0] = b0.x; mb[1] = b0.y; mb[2] = b0.z; mb[3] = b0.w;
-            mb[4] = b1.x; mb[5] = b1.y; mb[6] = b1.z; mb[7] = b1.w;
-        }
 #pragma unroll
         for (int r = 0; r < R; ++r) fin = fin && __builtin_isfinite(ma[r]) && ma[r] > 0.f;
 #pragma unroll
@@ -2403,7 +2412,6 @@ __global__ __launch_bounds__(kGrp8Block) void newton8_fwd_group_kernel(const voi
     fin = gsum_lanes<G>(fin ? 0.f : 1.f) == 0.f;  // the whole problem
     const float poison = fin ? 0.f : __builtin_nanf("");
     // initial point (column centring), as in the throughput kernel's init_batch
-    float beta[7], T[R][8], a[R];
     {
         float cm[8];
 #pragma unroll
@@ -2507,7 +2515,7 @@ __global__ __launch_bounds__(kGrp8Block) void newton8_fwd_group_kernel(const voi
     float gmax = gmax_of();
     const bool conv0 = OT ? ot_within_tol8(g, mb, tol, sa, sb) : gmax <= tol;
     bool active = valid && !conv0 && fin && max_iter > 0;
-    int status = !fin ? BIRKHOFF4_NON_FINITE : (conv0 ? 0 : BIRKHOFF4_NOT_CONVERGED);
+    status = !fin ? BIRKHOFF4_NON_FINITE : (conv0 ? 0 : BIRKHOFF4_NOT_CONVERGED);
     weights();
 #pragma unroll
     for (int j = 0; j < 7; ++j) ga[j] = g[j];
@@ -2593,25 +2601,117 @@ __global__ __launch_bounds__(kGrp8Block) void newton8_fwd_group_kernel(const voi
             }
         }
     }
-    if (!valid) return;
+    return out;
+}
+
+template <int R, bool WRITE_DUAL, bool WRITE_ITERS, bool OT>
+__device__ __forceinline__ void store_group8(float* __restrict__ P, float* __restrict__ dual, int32_t* __restrict__ iters,
+                                             int64_t b, int q, const GroupProblem<R>& g, const float ma[R], float eta) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int i = R * q + r;
         v4f* pp = reinterpret_cast<v4f*>(P) + 16 * b + 2 * i;
         const float m = OT ? ma[r] : 1.f;
-        pp[0] = v4f{m * T[r][0], m * T[r][1], m * T[r][2], m * T[r][3]};
-        pp[1] = v4f{m * T[r][4], m * T[r][5], m * T[r][6], m * T[r][7]};
+        pp[0] = v4f{m * g.T[r][0], m * g.T[r][1], m * g.T[r][2], m * g.T[r][3]};
+        pp[1] = v4f{m * g.T[r][4], m * g.T[r][5], m * g.T[r][6], m * g.T[r][7]};
         if constexpr (WRITE_DUAL) {
-            float x = beta[0] * 0.f;  // beta_8 = 0, NaN if poisoned
+            float x = g.beta[0] * 0.f;  // beta_8 = 0, NaN if poisoned
 #pragma unroll
-            for (int j = 0; j < 7; ++j) x = i == j ? beta[j] : x;
+            for (int j = 0; j < 7; ++j) x = i == j ? g.beta[j] : x;
             const float e2 = OT ? eta * kLn2 : kLn2;
-            dual[16 * b + i] = OT ? e2 * (lg2(m) - a[r]) : -a[r] * e2;
+            dual[16 * b + i] = OT ? e2 * (lg2(m) - g.a[r]) : -g.a[r] * e2;
             dual[16 * b + 8 + i] = i < 7 ? x * e2 : x;
         }
     }
     if constexpr (WRITE_ITERS)
-        if (q == 0) iters[b] = status;
+        if (q == 0) iters[b] = g.status;
+}
+
+template <int R, int DT, bool WRITE_DUAL, bool WRITE_ITERS, bool OT>
+__global__ __launch_bounds__(kGrp8Block) void newton8_fwd_group_kernel(const void* __restrict__ H,
+                                                                       float* __restrict__ P, float* __restrict__ dual,
+                                                                       int32_t* __restrict__ iters, int64_t B,
+                                                                       float tol, int max_iter,
+                                                                       const float* __restrict__ av,
+                                                                       const float* __restrict__ bv, float eta) {
+    constexpr int G = 8 / R;                        // lanes per problem
+    const float hsc = OT ? -kLog2e / eta : kLog2e;  // log2-unit logits per unit of H (or of M)
+    const int64_t b = static_cast<int64_t>(blockIdx.x) * (kGrp8Block / G) + threadIdx.x / G;  // this group's problem
+    const int q = threadIdx.x % G;  // this lane's rows: R q .. R q + R - 1
+    const bool valid = b < B;       // uniform across the group
+    float h[R][8], ma[R], mb[8];    // logits; OT: these rows' masses and all column masses
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) h[r][j] = 0.f;
+        ma[r] = 1.f;
+        if (valid) {
+            load_row8<DT>(H, b, R * q + r, h[r]);
+            if constexpr (OT) ma[r] = av[8 * b + R * q + r];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) mb[j] = 1.f;
+    if constexpr (OT)
+        if (valid) {
+            const v4f b0 = reinterpret_cast<const v4f*>(bv)[2 * b], b1 = reinterpret_cast<const v4f*>(bv)[2 * b + 1];
+            mb[0] = b0.x; mb[1] = b0.y; mb[2] = b0.z; mb[3] = b0.w;
+            mb[4] = b1.x; mb[5] = b1.y; mb[6] = b1.z; mb[7] = b1.w;
+        }
+    const GroupProblem<R> g = group_project8<R, OT>(h, ma, mb, hsc, valid, tol, max_iter);
+    if (valid) store_group8<R, WRITE_DUAL, WRITE_ITERS, OT>(P, dual, iters, b, q, g, ma, eta);
+}
+
+// Residual mixing of few tokens: the projection and the mixing in one launch, a wave per
+// 64-chunk column of a token. Every quad (n = 8: group of eight lanes) of the wave projects the
+// token's matrix, by the same code as the latency variants, so P has the same bits, while the
+// column's loads are in flight; the column-0 wave writes P, dual and status. While the waves
+// are few the repeated projections cost nothing and a launch is saved: 96 tokens of 4 x 4096
+// bf16 channels, N(0,1) logits, 7.3 us as two launches, 4.6 as one.
+template <int DX, int DT, int N, bool WRITE_DUAL, bool WRITE_ITERS>
+__global__ __launch_bounds__(64) void mix_small_kernel(const void* __restrict__ H, const v4u* __restrict__ X,
+                                                       v4u* __restrict__ Y, float* __restrict__ P,
+                                                       float* __restrict__ dual, int32_t* __restrict__ iters, int64_t nc,
+                                                       float tol, int max_iter) {
+    const int64_t t = blockIdx.x, col = 64 * static_cast<int64_t>(blockIdx.y);
+    const unsigned lane = threadIdx.x;
+    const int q = lane % N;  // this lane's row
+    const int64_t off = N * nc * t + col;
+    const bool own = lane < nc - col;
+    v4u x[N], y[N];
+    float h[1][N];
+    if constexpr (N == 4)
+        load_row<DT>(H, t, q, h[0]);
+    else
+        load_row8<DT>(H, t, q, h[0]);
+#pragma unroll
+    for (int j = 0; j < N; ++j) x[j] = v4u{0u, 0u, 0u, 0u};
+    if (own) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) x[j] = __builtin_nontemporal_load(X + (off + j * nc) + lane);
+    }
+    float p[N * N];  // row i from lane i, uniform
+    auto gather = [&](const float T[N]) {
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int j = 0; j < N; ++j) p[N * i + j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(T[j]), i));
+    };
+    if constexpr (N == 4) {
+        const QuadProblem r = quad_project(h[0], true, tol, max_iter);
+        if (col == 0 && lane < 4) store_quad<WRITE_DUAL, WRITE_ITERS>(P, dual, iters, t, q, r);
+        gather(r.T);
+    } else {
+        const float ma[1] = {1.f}, mb[8] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
+        const GroupProblem<1> r = group_project8<1, false>(h, ma, mb, kLog2e, true, tol, max_iter);
+        if (col == 0 && lane < 8) store_group8<1, WRITE_DUAL, WRITE_ITERS, false>(P, dual, iters, t, q, r, ma, 1.f);
+        gather(r.T[0]);
+    }
+    mix_chunk<DX, N>(p, x, y);
+    if (own) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) __builtin_nontemporal_store(y[j], Y + (off + j * nc) + lane);
+    }
 }
 
 // Backward for n = 8 (eq. derivative, a = b = 1, eta = 1), the flow form of the 4 x 4
@@ -3561,6 +3661,39 @@ int launch_mix_fwd(const float* P, const void* X, void* Y, int64_t B, int64_t nc
     return launch_status();
 }
 
+// Waves up to which the fused call is taken: beyond, the repeated projections fill the SIMDs. us
+// fused / as two launches, 4 x 4096 bf16 channels, logits N(0,1) and N(0,10^2): 768 waves 4.6 /
+// 7.3 and 7.0 / 9.6; 2048 waves 5.7 / 7.9 and 11.3 / 12.3; 4096 waves 9.4 / 10.9 and 17.4 / 14.4.
+// 8 x 4096: 768 waves 8.8 / 12.0 and 16.1 / 19.5; 8 x 256: 1024 waves 8.8 / 12.0 and 18.9 / 22.8, 2048
+// waves 12.8 / 12.5 and 26.7 / 25.4.
+template <int N>
+constexpr int64_t mix_small_waves() { return N == 4 ? 2048 : 1024; }
+
+template <int N>
+bool mix_small(int64_t B, int64_t nc) {
+    const int64_t cols = (nc + 63) / 64, most = mix_small_waves<N>();
+    return nc > 0 && B <= most && cols <= most && B * cols <= most;
+}
+
+template <int N, int DX, int DT>
+int launch_mix_small(const void* H, const void* X, void* Y, float* P, float* dual, int32_t* iters, int64_t B,
+                     int64_t nc, float tol, int max_iter, hipStream_t stream) {
+    auto kern = dual ? (iters ? mix_small_kernel<DX, DT, N, true, true> : mix_small_kernel<DX, DT, N, true, false>)
+                     : (iters ? mix_small_kernel<DX, DT, N, false, true> : mix_small_kernel<DX, DT, N, false, false>);
+    launch_kernel(kern, dim3(static_cast<unsigned>(B), static_cast<unsigned>((nc + 63) / 64)), dim3(64), 0, stream, H,
+                  static_cast<const v4u*>(X), static_cast<v4u*>(Y), P, dual, iters, nc, tol, max_iter);
+    return launch_status();
+}
+
+template <int N>
+int launch_mix_small(const void* H, int h_dtype, const void* X, int x_dtype, void* Y, float* P, float* dual,
+                     int32_t* iters, int64_t B, int64_t nc, float tol, int max_iter, hipStream_t stream) {
+    constexpr int F = BIRKHOFF4_F32, S = BIRKHOFF4_BF16;
+    auto launch = x_dtype == S ? (h_dtype == S ? launch_mix_small<N, S, S> : launch_mix_small<N, S, F>)
+                               : (h_dtype == S ? launch_mix_small<N, F, S> : launch_mix_small<N, F, F>);
+    return launch(H, X, Y, P, dual, iters, B, nc, tol, max_iter, stream);
+}
+
 template <int DX, int N = 4>
 int launch_mix_bwd(const float* P, const void* X, const void* dY, void* dX, void* dH, bool h16, int64_t B, int64_t nc,
                    hipStream_t stream) {
@@ -3877,6 +4010,8 @@ int birkhoff4_mix_fwd(const void* H, int h_dtype, const void* X, int x_dtype, vo
         overlaps(H, nh, iters, ni) || overlaps(P, np, dual, nd) || overlaps(P, np, iters, ni) ||
         overlaps(dual, nd, iters, ni))
         return BIRKHOFF4_ERR_OVERLAP;
+    if (mix_small<4>(B, nc))
+        return launch_mix_small<4>(H, h_dtype, X, x_dtype, Y, P, dual, iters, B, nc, tol, max_iter, stream);
     // the projection checks and queues P first; the mixing kernel then reads it
     if (int e = birkhoff4_fwd_ex2(H, h_dtype, P, dual, iters, B, tol, max_iter, BIRKHOFF4_AUTO, stream)) return e;
     if (nc == 0) return BIRKHOFF4_OK;
@@ -3934,6 +4069,8 @@ int birkhoff8_mix_fwd(const void* H, int h_dtype, const void* X, int x_dtype, vo
         overlaps(H, nh, iters, ni) || overlaps(P, np, dual, nd) || overlaps(P, np, iters, ni) ||
         overlaps(dual, nd, iters, ni))
         return BIRKHOFF4_ERR_OVERLAP;
+    if (mix_small<8>(B, nc))
+        return launch_mix_small<8>(H, h_dtype, X, x_dtype, Y, P, dual, iters, B, nc, tol, max_iter, stream);
     if (int e = birkhoff8_fwd(H, h_dtype, P, dual, iters, B, tol, max_iter, stream)) return e;
     if (nc == 0) return BIRKHOFF4_OK;
     if (x_dtype == BIRKHOFF4_BF16) return launch_mix_fwd<BIRKHOFF4_BF16, 8>(P, X, Y, B, nc, stream);
