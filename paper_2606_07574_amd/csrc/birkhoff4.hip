@@ -372,9 +372,19 @@ __global__ __launch_bounds__(kFwdBlock) void newton_fwd_kernel(const void* __res
     if (threadIdx.x == 0) next_batch = kFwdWaves;  // wave w starts on batch w
     __syncthreads();
     if (wv >= nbatch) return;  // uniform across the wave
+    // Near the end the waves stop claiming in groups of four (one per SIMD), the last group
+    // never: when all run dry together, four waves per SIMD with a few live lanes each share its
+    // issue slots to the end; staggered, the full waves use the slots that a draining one leaves.
+    // Forward without the dual, us, all together / staggered: 3 * 10^6 log-uniform fp32 135 / 117,
+    // 2^20 of the bf16 mixture 44.8 / 40.2, 2^24 446 / 436, 2^20 of N(0,10^2) 57.5 / 55.2. With the
+    // dual, where write requests bound the kernel, it gains nothing (2^20 of N(0,1) 40.8 / 41.8).
+    const int keep = wv < 4 || WRITE_DUAL ? 0 : wv < 8 ? 6 : wv < 12 ? 14 : 24;  // batches left to the others
     auto claim = [&]() -> int32_t {
-        int32_t v = 0;
-        if (lane == 0) v = atomicAdd(&next_batch, 1);
+        int32_t v = nbatch;
+        if (lane == 0) {
+            const bool take = keep == 0 || nbatch - *const_cast<volatile int32_t*>(&next_batch) >= keep;
+            if (take) v = atomicAdd(&next_batch, 1);
+        }
         return __builtin_amdgcn_readfirstlane(v);
     };
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -1961,7 +1971,8 @@ __global__ __launch_bounds__(kB8Block, 2) void newton8_fwd_kernel(const void* __
                                                                 int32_t* __restrict__ iters, int64_t B, float tol,
                                                                 int max_iter,
                                                                 const float* __restrict__ av,
-                                                                const float* __restrict__ bv, float eta) {
+                                                                const float* __restrict__ bv, float eta, int rounds,
+                                                                int early) {
     constexpr int NW = RawWords8<DT>::n;
     constexpr int SLOT = OT ? kB8SlotOT : kB8Slot;
     const float hsc = OT ? -kLog2e / eta : kLog2e;  // log2-unit logits per unit of H (or of M)
@@ -1987,17 +1998,24 @@ __global__ __launch_bounds__(kB8Block, 2) void newton8_fwd_kernel(const void* __
     // other without draining in between, and all waves run out of batches together.
     const int64_t gw = static_cast<int64_t>(blockIdx.x) * kB8Waves + wv;
     const int64_t nwv = static_cast<int64_t>(gridDim.x) * kB8Waves;
-    if (gw * kB8Ring >= B) return;  // uniform across the wave
-    // A problem is named by kB8Ring k + p for position p of the wave's k-th batch.
-    auto problem = [&](int32_t id) -> int64_t {
-        return (static_cast<int64_t>(id / kB8Ring) * nwv + gw) * kB8Ring + id % kB8Ring;
+    // The blocks from `early` on end with the first `rounds` batches of each wave; the remaining
+    // batches go round the waves of the earlier blocks alone.
+    const int64_t ewv = static_cast<int64_t>(early) * kB8Waves;
+    // First problem of the wave's k-th batch, B or more if there is none.
+    auto batch_start = [&](int32_t k) -> int64_t {
+        if (k < rounds) return (static_cast<int64_t>(k) * nwv + gw) * kB8Ring;
+        if (gw >= ewv) return B;
+        return (static_cast<int64_t>(rounds) * nwv + static_cast<int64_t>(k - rounds) * ewv + gw) * kB8Ring;
     };
+    // A problem is named by kB8Ring k + p for position p of the wave's k-th batch.
+    auto problem = [&](int32_t id) -> int64_t { return batch_start(id / kB8Ring) + id % kB8Ring; };
 
     // Raw words of the batch to initialise next (two lanes per problem), one batch ahead.
     uint32_t raw[NW];
 #pragma unroll
     for (int q = 0; q < NW; ++q) raw[q] = 0u;
-    int64_t bnext = gw * kB8Ring;  // first problem of that batch (uniform)
+    int64_t bnext = batch_start(0);  // first problem of that batch (uniform)
+    if (bnext >= B) return;          // uniform across the wave
     int32_t knext = 0;             // its index in the wave's sequence
     v4f pa = {1.f, 1.f, 1.f, 1.f}, pb0 = pa, pb1 = pa;  // OT: its marginals (this lane's four a_i, all b_j)
     auto prefetch = [&]() {
@@ -2158,8 +2176,8 @@ __global__ __launch_bounds__(kB8Block, 2) void newton8_fwd_kernel(const void* __
             if constexpr (WRITE_ITERS)
                 if (hf == 0) iters[bp] = !fin ? BIRKHOFF4_NON_FINITE : (conv ? 0 : BIRKHOFF4_NOT_CONVERGED);
         }
-        bnext += nwv * kB8Ring;
         ++knext;
+        bnext = batch_start(knext);
         prefetch();
     };
 
@@ -3025,12 +3043,16 @@ __device__ __forceinline__ void ot_store(float* __restrict__ T, float* __restric
     if constexpr (WRITE_ITERS) iters[p] = status;
 }
 
+struct OtRanges {  // problems per wave of each class
+    int64_t n[4];
+};
+
 template <bool WRITE_DUAL, bool WRITE_ITERS>
 __global__ __launch_bounds__(kOtBlock) void ot4_fwd_kernel(const float* __restrict__ M, const float* __restrict__ av,
                                                           const float* __restrict__ bv, float eta,
                                                           float* __restrict__ T, float* __restrict__ dual,
                                                           int32_t* __restrict__ iters, int64_t B, float tol,
-                                                          int max_iter, int64_t per_wave) {
+                                                          int max_iter, OtRanges per, int64_t members) {
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -3038,9 +3060,17 @@ __global__ __launch_bounds__(kOtBlock) void ot4_fwd_kernel(const float* __restri
     // a (6), b (7) of a problem not finished at its initial point.
     __shared__ v4f ring_all[kOtWaves][64 * kOtSlot];
     v4f* const ring = ring_all[wv];
-    const int64_t r0 = (static_cast<int64_t>(blockIdx.x) * kOtWaves + wv) * per_wave;
+    // Wave ranges in four classes of `members` waves, the class's length each (one class of
+    // any number: per.n[0] each).
+    const int64_t gw = static_cast<int64_t>(blockIdx.x) * kOtWaves + wv;
+    const int cls = members > 0 ? static_cast<int>(gw / members) : 0;
+    int64_t r0 = 0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) r0 += c < cls ? members * per.n[c] : 0;
+    const int64_t len = per.n[cls < 3 ? cls : 3];
+    r0 += (gw - members * cls) * len;
     if (r0 >= B) return;  // uniform across the wave
-    const int64_t r1 = (r0 + per_wave < B) ? r0 + per_wave : B;
+    const int64_t r1 = (r0 + len < B) ? r0 + len : B;
     int64_t bnext = r0;        // first problem of the next batch to initialise (uniform)
     int nfresh = 0, icur = 0;  // ring slots [icur, nfresh) not yet taken
     const float rsc = -kLog2e / eta;
@@ -3522,11 +3552,23 @@ int launch_fwd8(const void* H, float* P, float* dual, int32_t* iters, int64_t B,
     int64_t grid = static_cast<int64_t>(cus) * fwd8_blocks_per_cu<DT, WD, WI, OT>(dev);
     const int64_t needed = (batches + kB8Waves - 1) / kB8Waves;
     if (grid > needed) grid = needed;
+    // With two resident blocks per CU the second ones end some batches per wave before the first
+    // (as the 4 x 4 forward's waves stagger), once there are rounds enough to take them from. us,
+    // together / staggered: 131072 problems N(0,1) (2 rounds) 28.2 / 30.2; OT 2 * 10^5 (3) 67 / 73
+    // and 4 * 10^5 (6) 108 / 100; mixture bf16 3 * 10^5 (4) 80.0 / 75.8, 10^6 (15) 189.6 / 183.9; N(0,1)
+    // 2^20 (16) 162 / 150 with three batches; mixture 2^22 (64) 788 / 785 with three, 779 with six.
+    const int64_t waves = grid * kB8Waves, full = batches / waves;
+    const int64_t stagger = grid != 2 * static_cast<int64_t>(cus) || full < 4 ? 0 : full < 7 ? 2 : full < 32 ? 3 : 6;
+    const int64_t early = stagger > 0 ? cus : grid;
+    const int64_t rounds =
+        stagger > 0 ? (batches - stagger * early * kB8Waves) / waves : (batches + waves - 1) / waves;
+    const int64_t left = batches - rounds * waves;
     // a problem is named in 32 bits by its wave's batch count and its position in the batch
-    const int64_t per_wave = (batches + grid * kB8Waves - 1) / (grid * kB8Waves);
-    if (per_wave > INT32_MAX / kB8Ring) return BIRKHOFF4_ERR_SIZE;
+    const int64_t most = rounds + (left > 0 ? (left + early * kB8Waves - 1) / (early * kB8Waves) : 0);
+    if (most > INT32_MAX / kB8Ring) return BIRKHOFF4_ERR_SIZE;
     launch_kernel((newton8_fwd_kernel<DT, WD, WI, OT>), dim3(static_cast<unsigned>(grid)), dim3(kB8Block), 0,
-                  stream, H, P, dual, iters, B, tol, max_iter, a, b, eta);
+                  stream, H, P, dual, iters, B, tol, max_iter, a, b, eta, static_cast<int>(rounds),
+                  static_cast<int>(early));
     return launch_status();
 }
 
@@ -3557,10 +3599,21 @@ int launch_ot_fwd(const float* M, const float* a, const float* b, float eta, flo
     int64_t per_wave = (B + ranges - 1) / ranges;
     if (per_wave < 64) per_wave = 64;
     if (per_wave < waves_min) per_wave = waves_min;
-    const int64_t waves = (B + per_wave - 1) / per_wave;
+    int64_t waves = (B + per_wave - 1) / per_wave;
+    OtRanges per = {{per_wave, per_wave, per_wave, per_wave}};
+    int64_t members = 0;
+    // The four resident blocks of a CU end one after the other instead of together, so that the
+    // full waves use the issue slots that draining ones leave; the lengths differ by what each
+    // remaining block takes of the eight batches of 64 between two ends. us at eta = 0.5, together
+    // / staggered: 8 * 10^5 problems 59.7 / 52.6, 2^20 69.8 / 63.9, 1.5 * 10^6 94.5 / 90.0.
+    if (B < kOtManyB && per_wave >= 192) {
+        members = kOtRanges / 4;
+        waves = kOtRanges;
+        per = {{per_wave + 139, per_wave + 11, per_wave - 53, per_wave - 97}};
+    }
     const int64_t grid = (waves + kOtWaves - 1) / kOtWaves;
     launch_kernel((ot4_fwd_kernel<WD, WI>), dim3(static_cast<unsigned>(grid)), dim3(kOtBlock), 0, stream, M, a,
-                       b, eta, T, dual, iters, B, tol, max_iter, per_wave);
+                       b, eta, T, dual, iters, B, tol, max_iter, per, members);
     return launch_status();
 }
 
