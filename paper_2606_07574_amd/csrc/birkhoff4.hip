@@ -2755,12 +2755,18 @@ using MaybeRestrict = std::conditional_t<IN_PLACE, T*, T* __restrict__>;
 
 // DO: dH stored as fp32 or, rounded to nearest even, as bf16 (as in the 4 x 4 backward; 10^6
 // problems, fp32 dP: forward + backward + conversion 366 us, forward + backward 291 us).
+// Blocks of one wave: each takes the next chunk as soon as a wave's registers and tile are free.
+// OT, four waves per block and dP loaded after P / one wave and both loaded first: 4096 problems 8.4 /
+// 7.5 us, 2 * 10^5 34.3 / 30.4, 10^6 136.7 / 132.9; projection with bf16 dH 4 * 10^5 51.7 / 44.7.
+// (10^5, which the last-level cache holds: 15.5 / 16.2.)
+constexpr int kB8BwdWaves = 1;
+
 template <int DT, int DO, bool OT, bool IN_PLACE = false>
-__global__ __launch_bounds__(kB8Block, 2) void implicit8_bwd_kernel(const float* __restrict__ P,
+__global__ __launch_bounds__(64 * kB8BwdWaves, 2) void implicit8_bwd_kernel(const float* __restrict__ P,
                                                                      MaybeRestrict<IN_PLACE, const void> dP,
                                                                      MaybeRestrict<IN_PLACE, void> dH, int64_t B,
                                                                      const float* __restrict__ av, float eta) {
-    __shared__ v4f tile_all[kB8Waves][64 * kB8Stride];
+    __shared__ v4f tile_all[kB8BwdWaves][64 * kB8Stride];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     v4f* const tile = tile_all[wv];
@@ -2771,23 +2777,28 @@ __global__ __launch_bounds__(kB8Block, 2) void implicit8_bwd_kernel(const float*
     constexpr int GP = (DT == BIRKHOFF4_BF16) ? 8 : 16;  // 16-byte pieces of dP per problem
     constexpr int HP = (DO == BIRKHOFF4_BF16) ? 8 : 16;  // 16-byte pieces of dH per problem
     const int64_t nchunk = (B + 63) / 64;
-    for (int64_t c = static_cast<int64_t>(blockIdx.x) * kB8Waves + wv; c < nchunk;
-         c += static_cast<int64_t>(gridDim.x) * kB8Waves) {
+    for (int64_t c = static_cast<int64_t>(blockIdx.x) * kB8BwdWaves + wv; c < nchunk;
+         c += static_cast<int64_t>(gridDim.x) * kB8BwdWaves) {
         const int64_t base = c * 64;
         const int n = (B - base < 64) ? static_cast<int>(B - base) : 64;  // problems in this chunk
-        // P: 16 pieces per problem, piece k of the chunk goes to problem k / 16, slot k % 16
-        {
-            v4f pc[16];
+        // P and dP: every load first, 16 and GP pieces per problem; piece k of the chunk goes to
+        // problem k / 16, slot k % 16 (dP: k / GP, k % GP)
+        v4f pc[16];
+        v4u gc[GP];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int k = 64 * q + lane;
-                pc[q] = k < 16 * n ? __builtin_nontemporal_load(P4 + 16 * base + k) : v4f{0.f, 0.f, 0.f, 0.f};
-            }
+        for (int q = 0; q < 16; ++q) {
+            const int k = 64 * q + lane;
+            pc[q] = k < 16 * n ? __builtin_nontemporal_load(P4 + 16 * base + k) : v4f{0.f, 0.f, 0.f, 0.f};
+        }
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int k = 64 * q + lane;
-                tile[(k >> 4) * kB8Stride + (k & 15)] = pc[q];
-            }
+        for (int q = 0; q < GP; ++q) {
+            const int k = 64 * q + lane;
+            gc[q] = k < GP * n ? __builtin_nontemporal_load(G4 + GP * base + k) : v4u{0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int k = 64 * q + lane;
+            tile[(k >> 4) * kB8Stride + (k & 15)] = pc[q];
         }
         __builtin_amdgcn_wave_barrier();
         float T[64];
@@ -2797,19 +2808,11 @@ __global__ __launch_bounds__(kB8Block, 2) void implicit8_bwd_kernel(const float*
             T[4 * r] = t.x; T[4 * r + 1] = t.y; T[4 * r + 2] = t.z; T[4 * r + 3] = t.w;
         }
         __builtin_amdgcn_wave_barrier();
-        // dP: GP pieces per problem, kept in the tile (read twice below)
-        {
-            v4u gc[GP];
+        // dP stays in the tile (read twice below)
 #pragma unroll
-            for (int q = 0; q < GP; ++q) {
-                const int k = 64 * q + lane;
-                gc[q] = k < GP * n ? __builtin_nontemporal_load(G4 + GP * base + k) : v4u{0u, 0u, 0u, 0u};
-            }
-#pragma unroll
-            for (int q = 0; q < GP; ++q) {
-                const int k = 64 * q + lane;
-                tileu[(k / GP) * kB8Stride + (k % GP)] = gc[q];
-            }
+        for (int q = 0; q < GP; ++q) {
+            const int k = 64 * q + lane;
+            tileu[(k / GP) * kB8Stride + (k % GP)] = gc[q];
         }
         __builtin_amdgcn_wave_barrier();
         // row i of this lane's G from the tile
@@ -3641,7 +3644,7 @@ int launch_bwd(Kernel kern, const float* P, const void* dP, void* dH, int64_t B,
 template <typename Kernel>
 int launch_bwd8(Kernel kern, const float* P, const void* dP, void* dH, int64_t B, hipStream_t stream,
                 const float* a = nullptr, float eta = 1.f) {
-    launch_kernel(kern, dim3(static_cast<unsigned>(bwd_grid(B, kB8Waves))), dim3(kB8Block), 0, stream, P, dP, dH, B, a,
+    launch_kernel(kern, dim3(static_cast<unsigned>(bwd_grid(B, kB8BwdWaves))), dim3(64 * kB8BwdWaves), 0, stream, P, dP, dH, B, a,
                   eta);
     return launch_status();
 }
