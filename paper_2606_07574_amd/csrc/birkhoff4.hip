@@ -1409,7 +1409,7 @@ __global__ __launch_bounds__(64 * mix_bwd_max_waves(N)) void mix_bwd_kernel(cons
 
 // Short rows, nc <= L with L = 8, 16 or 32: L lanes per token, 64 / L tokens per wave, one
 // chunk of every row per lane, P read per lane. A wave of its own for each token would leave
-// most lanes idle: MIX_SHORT.
+// most lanes idle: 3 * 10^4 tokens of 4 x 128 bf16 channels forward 14.9 -> 11.5 us, backward 56.2 -> 17.3.
 constexpr int kMixShortBlock = 256;
 
 template <int N>
