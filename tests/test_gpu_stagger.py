@@ -62,16 +62,43 @@ def test_ot(B):
     same_copies(dual, n)
 
 
-# 8 x 8: 2048 waves of 32-problem batches; no stagger below 4 full rounds, then 2, 3 and 6 batches
-@pytest.mark.parametrize("rounds", [2, 4, 7, 32])
-@pytest.mark.parametrize("off", [-1, 0, 33])
-def test_projection8(rounds, off):
-    B = 65536 * rounds + off
+# 8 x 8: 2048 waves of 32-problem batches; no stagger below 4 full rounds, then 2, 3 and 6 batches.
+# Per line: one batch short of it, the line, a ragged size past it, and the last size of the
+# round, whose remainder gives the early blocks the most extra batches.
+SIZES8 = [65536 * r + off for r in (4, 7, 32) for off in (-32, 0, 33, 65536 - 33)]
+
+
+@pytest.mark.parametrize("B", [131072 + 33] + SIZES8)
+def test_projection8(B):
     say(f"test: staggered 8x8 forward, B={B}")
-    rng = np.random.default_rng(rounds)
+    rng = np.random.default_rng(B)
     H = np.concatenate([s * rng.standard_normal((301, 8, 8)) for s in (1.0, 10.0)]).astype(np.float32)
     n = H.shape[0]
-    P, _, it = b4.fwd8(repeated(H, B), want_dual=False, want_iters=True)
+    Hd = repeated(H, B)
+    P, _, it = b4.fwd8(Hd, want_dual=False, want_iters=True)
     assert (it >= 0).all()
     assert np.abs(P[:n].cpu().numpy() - on.fwd(H.astype(np.float64))[0]).max() <= TOL_P
     same_copies(P, n)
+    same_copies(it, n)
+    P2, dual, _ = b4.fwd8(Hd)
+    assert torch.equal(P2, P)
+    same_copies(dual, n)
+
+
+@pytest.mark.parametrize("B", [65536 * 4 - 32, 65536 * 5 - 33, 65536 * 6 + 1])
+def test_ot8(B):
+    say(f"test: staggered 8x8 OT forward, B={B}")
+    rng = np.random.default_rng(B)
+    n = 601
+    M = (2.0 * rng.standard_normal((n, 8, 8))).astype(np.float32)
+    a = rng.uniform(0.2, 2.0, (n, 8)).astype(np.float32)
+    b = rng.uniform(0.2, 2.0, (n, 8))
+    b = (b * (a.astype(np.float64).sum(1) / b.sum(1))[:, None]).astype(np.float32)
+    T, dual, it = b4.ot8_fwd(*(repeated(x, B) for x in (M, a, b)), 0.5, want_iters=True)
+    assert (it >= 0).all()
+    b64 = b.astype(np.float64)
+    b64 *= (a.astype(np.float64).sum(1) / b64.sum(1))[:, None]
+    ref = on.ot_fwd(M.astype(np.float64), a.astype(np.float64), b64, 0.5)[0]
+    assert np.abs(T[:n].cpu().numpy() - ref).max() <= 2e-5  # as above
+    for t in (T, dual, it):
+        same_copies(t, n)
