@@ -1721,10 +1721,11 @@ __global__ __launch_bounds__(kSkBlock) void sk_bwd_reg_kernel(const void* __rest
 // lane. The forward is the 4 x 4 kernel's iteration written for 7 free potentials (the
 // row-softmax state in product form, trial steps capped in spread, Armijo with the
 // rounding-noise test, Levenberg-Marquardt shift, re-derivation of flushed entries). A
-// wave takes every nwv-th batch of 32 problems (nwv the resident waves of the grid); it
-// initialises a batch with all its lanes (two lanes per problem) into an LDS ring, and a
-// lane whose problem finishes takes the next one from the ring at once. The Newton system is the column Laplacian with 28 weights,
-// grounded at column 8 and solved by subtraction-free elimination of nodes 1..7.
+// wave takes every nwv-th batch of 32 problems (nwv the resident waves of the grid; the last
+// batches go to half of the waves, see the launcher); it initialises a batch with all its lanes
+// (two lanes per problem) into an LDS ring, and a lane whose problem finishes takes the next one
+// from the ring at once. The Newton system is the column Laplacian with 28 weights, grounded at
+// column 8 and solved by subtraction-free elimination of nodes 1..7.
 // ---------------------------------------------------------------------------
 constexpr int kB8Block = 256;
 constexpr int kB8Waves = kB8Block / 64;
@@ -1995,8 +1996,8 @@ __global__ __launch_bounds__(kB8Block, 2) void newton8_fwd_kernel(const void* __
     int32_t* const order = order_all[wv];
     v4f* const marg = marg_all[OT ? wv : 0] + (OT ? 4 * lane : 0);
     // The grid is the resident waves. Wave gw of the grid's nwv takes the batches of kB8Ring
-    // problems gw, gw + nwv, gw + 2 nwv, ...: it refills its lanes from one batch after the
-    // other without draining in between, and all waves run out of batches together.
+    // problems gw, gw + nwv, gw + 2 nwv, ... and refills its lanes from one batch after the other
+    // without draining in between.
     const int64_t gw = static_cast<int64_t>(blockIdx.x) * kB8Waves + wv;
     const int64_t nwv = static_cast<int64_t>(gridDim.x) * kB8Waves;
     // The blocks from `early` on end with the first `rounds` batches of each wave; the remaining
@@ -3543,7 +3544,7 @@ int launch_fwd8_group(const void* H, float* P, float* dual, int32_t* iters, int6
     return launch_status();
 }
 
-// n = 8: the grid is the resident waves (fewer for small B), each taking every nwv-th batch.
+// n = 8: the grid is the resident waves (fewer for small B).
 template <int DT, bool WD, bool WI, bool OT = false>
 int launch_fwd8(const void* H, float* P, float* dual, int32_t* iters, int64_t B, float tol, int max_iter,
                 hipStream_t stream, const float* a = nullptr, const float* b = nullptr, float eta = 1.f) {
@@ -3569,10 +3570,17 @@ int launch_fwd8(const void* H, float* P, float* dual, int32_t* iters, int64_t B,
     const int64_t needed = (batches + kB8Waves - 1) / kB8Waves;
     if (grid > needed) grid = needed;
     // With two resident blocks per CU the second ones end some batches per wave before the first
-    // (as the 4 x 4 forward's waves stagger), once there are rounds enough to take them from. us,
-    // together / staggered: 131072 problems N(0,1) (2 rounds) 28.2 / 30.2; OT 2 * 10^5 (3) 67 / 73
-    // and 4 * 10^5 (6) 108 / 100; mixture bf16 3 * 10^5 (4) 80.0 / 75.8, 10^6 (15) 189.6 / 183.9; N(0,1)
-    // 2^20 (16) 162 / 150 with three batches; mixture 2^22 (64) 788 / 785 with three, 779 with six.
+    // (as the 4 x 4 forward's waves stagger), once there are rounds enough to take them from: the
+    // late waves are given `stagger` batches more than the early ending ones, and whatever part
+    // of a round is left over, so that they end `stagger` to `stagger` + 2 batches later. us,
+    // together / staggered, fp32: N(0,1) 131072 problems (2 rounds) 28.2 / 30.2; OT 2 * 10^5 (3)
+    // 67 / 73. From four rounds on it is never slower, whichever part of a round is left:
+    //    rounds       4.0          4.5          4.99         5.99         6.99         7.0          31.99     64.99
+    //    N(0,1)       40.8/40.3    45.0/43.7    51.3/49.9    57.7/55.6    67.2/63.6    67.0/63.8    289/285   566/560
+    //    mixture      73.9/72.4    78.7/74.6    86.8/78.8    95.5/85.9    105/96.2     103/95.4     386/381   735/724
+    //    OT, eta 0.5  77.0/71.6    81.2/78.7    89.7/87.0    103/96.5     117/109      114/106      450/437   889/871
+    // (Rounds to the nearest instead, for a lag of `stagger` +- 1: 4.75 rounds N(0,1) 47.2 against
+    // 49.5 but mixture 80.0 against 78.9, 4.99 rounds mixture 86.1 against 80.3.)
     const int64_t waves = grid * kB8Waves, full = batches / waves;
     const int64_t stagger = grid != 2 * static_cast<int64_t>(cus) || full < 4 ? 0 : full < 7 ? 2 : full < 32 ? 3 : 6;
     const int64_t early = stagger > 0 ? cus : grid;
