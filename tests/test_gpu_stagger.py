@@ -25,8 +25,10 @@ def same_copies(t, n):
     assert torch.equal(t[full:], t[:t.shape[0] - full])
 
 
-# 4 x 4: blocks of one CU share its batches; waves leave the last 24, 14 and 6 to others
-@pytest.mark.parametrize("B", [32769, 100003, 16384 * 7 - 1, 16384 * 15 + 1, 16384 * 25, 1 << 20, 3000001])
+# 4 x 4: blocks of one CU share its batches of 64; past sixteen of them, half and a quarter of the
+# rest (at most 24 and 14) are left to the other waves. 16384 problems are one batch per block.
+@pytest.mark.parametrize("B", [32769, 100003, 16384 * 7 - 1, 16384 * 16, 16384 * 16 + 1, 16384 * 18, 16384 * 20,
+                               16384 * 25, 16384 * 32 + 77, 1 << 20, 16384 * 72 + 5, 3000001])
 def test_projection(B):
     say(f"test: staggered 4x4 forward, B={B}")
     H = np.concatenate([workloads.gauss(401, s, seed=5)[0] for s in (1.0, 10.0, 50.0)])
