@@ -2950,10 +2950,15 @@ constexpr int kOtWaves = kOtBlock / 64;
 constexpr int kOtSlot = 8;  // v4f per ring slot
 // Wave ranges per launch: 4096 waves are resident, and a range should be long enough that the
 // lanes refill many times before it drains; past kOtManyB problems two ranges per slot even out
-// the waves. us at eta = 0.5 with 4096 / 8192 / 16384 ranges: 4 * 10^5 problems 38.8 / 39.2 /
-// 39.0, 2^20 68.4 / 70.6 / 77.3, 2 * 10^6 123.8 / 121.7 / 127.4, 2^22 241 / 232 / 236.
+// the waves, and ranges that would be shorter than kOtMinRange drain for most of their time: one
+// batch of 64 each then, for the hardware to balance. us with 4096 / 8192 / 16384 ranges, eta =
+// 0.5: 2^20 problems 68.4 / 70.6 / 77.3, 2 * 10^6 123.8 / 121.7 / 127.4, 2^22 241 / 232 / 236; with 4096 /
+// batches of 64, eta = 0.25, 0.5 and 1: 3 * 10^5 43.9 / 42.6, 34.5 / 32.9, 27.8 / 26.4; 3.8 * 10^5 47.1 /
+// 47.8, 38.2 / 35.9, 30.3 / 28.9; 4.3 * 10^5 50.2 / 52.6, 39.5 / 38.9, 31.7 / 31.7; 4.6 * 10^5 51.6 / 55.5, 40.4 /
+// 41.6, 32.0 / 33.2.
 constexpr int64_t kOtRanges = 4096;
 constexpr int64_t kOtManyB = 3 * (int64_t(1) << 19);
+constexpr int64_t kOtMinRange = 112;
 
 __device__ __forceinline__ v4f load4(const float* base, int64_t b) { return reinterpret_cast<const v4f*>(base)[b]; }
 
@@ -3055,16 +3060,17 @@ __device__ __forceinline__ void ot_store(float* __restrict__ T, float* __restric
     if constexpr (WRITE_ITERS) iters[p] = status;
 }
 
-struct OtRanges {  // problems per wave of each class
-    int64_t n[4];
-};
+// Staggered ranges: four classes of kOtRanges / 4 waves, by how many problems theirs are longer
+// than the mean, and the sums of that over a wave of each class before.
+constexpr int kOtLonger[4] = {139, 11, -53, -97};
+static_assert(kOtLonger[0] + kOtLonger[1] + kOtLonger[2] + kOtLonger[3] == 0, "the ranges cover the batch");
 
 template <bool WRITE_DUAL, bool WRITE_ITERS>
 __global__ __launch_bounds__(kOtBlock) void ot4_fwd_kernel(const float* __restrict__ M, const float* __restrict__ av,
                                                           const float* __restrict__ bv, float eta,
                                                           float* __restrict__ T, float* __restrict__ dual,
                                                           int32_t* __restrict__ iters, int64_t B, float tol,
-                                                          int max_iter, OtRanges per, int64_t members) {
+                                                          int max_iter, int64_t per_wave, bool stagger) {
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -3072,15 +3078,21 @@ __global__ __launch_bounds__(kOtBlock) void ot4_fwd_kernel(const float* __restri
     // a (6), b (7) of a problem not finished at its initial point.
     __shared__ v4f ring_all[kOtWaves][64 * kOtSlot];
     v4f* const ring = ring_all[wv];
-    // Wave ranges in four classes of `members` waves, the class's length each (one class of
-    // any number: per.n[0] each).
-    const int64_t gw = static_cast<int64_t>(blockIdx.x) * kOtWaves + wv;
-    const int cls = members > 0 ? static_cast<int>(gw / members) : 0;
-    int64_t r0 = 0;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) r0 += c < cls ? members * per.n[c] : 0;
-    const int64_t len = per.n[cls < 3 ? cls : 3];
-    r0 += (gw - members * cls) * len;
+    // (classes by the block index and constants: with a division by the class size every call took
+    // 0.4 us more, eta = 0.5: 500 problems 15.4 -> 15.7 us)
+    constexpr int kMembers = kOtRanges / 4;
+    const int gw = static_cast<int>(blockIdx.x) * kOtWaves + wv;
+    int64_t r0 = gw * per_wave, len = per_wave;
+    if (stagger) {
+        const int cls = gw / kMembers, member = gw % kMembers;
+        const int longer = cls == 0 ? kOtLonger[0] : cls == 1 ? kOtLonger[1] : cls == 2 ? kOtLonger[2] : kOtLonger[3];
+        const int before = cls == 0   ? 0
+                           : cls == 1 ? kOtLonger[0]
+                           : cls == 2 ? kOtLonger[0] + kOtLonger[1]
+                                      : -kOtLonger[3];
+        r0 += before * kMembers + longer * member;
+        len += longer;
+    }
     if (r0 >= B) return;  // uniform across the wave
     const int64_t r1 = (r0 + len < B) ? r0 + len : B;
     int64_t bnext = r0;        // first problem of the next batch to initialise (uniform)
@@ -3624,23 +3636,17 @@ int launch_ot_fwd(const float* M, const float* a, const float* b, float eta, flo
     const int64_t waves_min = (B + kMaxGrid * kOtWaves - 1) / (kMaxGrid * kOtWaves);
     const int64_t ranges = B < kOtManyB ? kOtRanges : 2 * kOtRanges;
     int64_t per_wave = (B + ranges - 1) / ranges;
-    if (per_wave < 64) per_wave = 64;
+    if (per_wave < kOtMinRange) per_wave = 64;
     if (per_wave < waves_min) per_wave = waves_min;
-    int64_t waves = (B + per_wave - 1) / per_wave;
-    OtRanges per = {{per_wave, per_wave, per_wave, per_wave}};
-    int64_t members = 0;
     // The four resident blocks of a CU end one after the other instead of together, so that the
     // full waves use the issue slots that draining ones leave; the lengths differ by what each
     // remaining block takes of the eight batches of 64 between two ends. us at eta = 0.5, together
     // / staggered: 8 * 10^5 problems 59.7 / 52.6, 2^20 69.8 / 63.9, 1.5 * 10^6 94.5 / 90.0.
-    if (B < kOtManyB && per_wave >= 192) {
-        members = kOtRanges / 4;
-        waves = kOtRanges;
-        per = {{per_wave + 139, per_wave + 11, per_wave - 53, per_wave - 97}};
-    }
+    const bool stagger = B < kOtManyB && per_wave >= 192;
+    const int64_t waves = stagger ? kOtRanges : (B + per_wave - 1) / per_wave;
     const int64_t grid = (waves + kOtWaves - 1) / kOtWaves;
     launch_kernel((ot4_fwd_kernel<WD, WI>), dim3(static_cast<unsigned>(grid)), dim3(kOtBlock), 0, stream, M, a,
-                       b, eta, T, dual, iters, B, tol, max_iter, per, members);
+                       b, eta, T, dual, iters, B, tol, max_iter, per_wave, stagger);
     return launch_status();
 }
 

@@ -44,8 +44,9 @@ def test_projection(B):
     same_copies(dual, n)
 
 
-# 4 x 4 OT: four classes of waves from 192 problems per wave (4096 waves) up to 3 * 2^19 problems
-@pytest.mark.parametrize("B", [191 * 4096, 191 * 4096 + 1, 1 << 20, (1 << 20) + 77, 3 * (1 << 19) - 1, 3 * (1 << 19)])
+# 4 x 4 OT: ranges of 64 problems below 112 per wave (4096 waves), of equal length up to 191, then
+# four classes of waves up to 3 * 2^19 problems, and 8192 ranges
+@pytest.mark.parametrize("B", [64 * 4096 + 1, 111 * 4096, 111 * 4096 + 1, 191 * 4096, 191 * 4096 + 1, 1 << 20, (1 << 20) + 77, 3 * (1 << 19) - 1, 3 * (1 << 19)])
 def test_ot(B):
     say(f"test: staggered 4x4 OT forward, B={B}")
     rng = np.random.default_rng(B)
