@@ -2764,18 +2764,14 @@ using MaybeRestrict = std::conditional_t<IN_PLACE, T*, T* __restrict__>;
 
 // DO: dH stored as fp32 or, rounded to nearest even, as bf16 (as in the 4 x 4 backward; 10^6
 // problems, fp32 dP: forward + backward + conversion 366 us, forward + backward 291 us).
-// Blocks of one wave: each takes the next chunk as soon as a wave's registers and tile are free.
-// OT, four waves per block and dP loaded after P / one wave and both loaded first: 4096 problems 8.4 /
-// 7.5 us, 2 * 10^5 34.3 / 30.4, 10^6 136.7 / 132.9; projection with bf16 dH 4 * 10^5 51.7 / 44.7.
-// (10^5, which the last-level cache holds: 15.5 / 16.2.)
-constexpr int kB8BwdWaves = 1;
-
-template <int DT, int DO, bool OT, bool IN_PLACE = false>
-__global__ __launch_bounds__(64 * kB8BwdWaves, 2) void implicit8_bwd_kernel(const float* __restrict__ P,
-                                                                     MaybeRestrict<IN_PLACE, const void> dP,
-                                                                     MaybeRestrict<IN_PLACE, void> dH, int64_t B,
-                                                                     const float* __restrict__ av, float eta) {
-    __shared__ v4f tile_all[kB8BwdWaves][64 * kB8Stride];
+// Blocks of one wave, each taking the next chunk as soon as a wave's registers and tile are free,
+// with P and dP loaded together; or (WAVES = 4, see bwd8_four_waves) of four with dP loaded after P.
+template <int DT, int DO, bool OT, bool IN_PLACE = false, int WAVES = 1>
+__global__ __launch_bounds__(64 * WAVES, 2) void implicit8_bwd_kernel(const float* __restrict__ P,
+                                                                  MaybeRestrict<IN_PLACE, const void> dP,
+                                                                  MaybeRestrict<IN_PLACE, void> dH, int64_t B,
+                                                                  const float* __restrict__ av, float eta) {
+    __shared__ v4f tile_all[WAVES][64 * kB8Stride];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     v4f* const tile = tile_all[wv];
@@ -2786,24 +2782,27 @@ __global__ __launch_bounds__(64 * kB8BwdWaves, 2) void implicit8_bwd_kernel(cons
     constexpr int GP = (DT == BIRKHOFF4_BF16) ? 8 : 16;  // 16-byte pieces of dP per problem
     constexpr int HP = (DO == BIRKHOFF4_BF16) ? 8 : 16;  // 16-byte pieces of dH per problem
     const int64_t nchunk = (B + 63) / 64;
-    for (int64_t c = static_cast<int64_t>(blockIdx.x) * kB8BwdWaves + wv; c < nchunk;
-         c += static_cast<int64_t>(gridDim.x) * kB8BwdWaves) {
+    for (int64_t c = static_cast<int64_t>(blockIdx.x) * WAVES + wv; c < nchunk;
+         c += static_cast<int64_t>(gridDim.x) * WAVES) {
         const int64_t base = c * 64;
         const int n = (B - base < 64) ? static_cast<int>(B - base) : 64;  // problems in this chunk
-        // P and dP: every load first, 16 and GP pieces per problem; piece k of the chunk goes to
-        // problem k / 16, slot k % 16 (dP: k / GP, k % GP)
+        // P and dP: 16 and GP pieces per problem; piece k of the chunk goes to problem k / 16, slot
+        // k % 16 (dP: k / GP, k % GP)
         v4f pc[16];
         v4u gc[GP];
+        auto load_dp = [&]() {
+#pragma unroll
+            for (int q = 0; q < GP; ++q) {
+                const int k = 64 * q + lane;
+                gc[q] = k < GP * n ? __builtin_nontemporal_load(G4 + GP * base + k) : v4u{0u, 0u, 0u, 0u};
+            }
+        };
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             const int k = 64 * q + lane;
             pc[q] = k < 16 * n ? __builtin_nontemporal_load(P4 + 16 * base + k) : v4f{0.f, 0.f, 0.f, 0.f};
         }
-#pragma unroll
-        for (int q = 0; q < GP; ++q) {
-            const int k = 64 * q + lane;
-            gc[q] = k < GP * n ? __builtin_nontemporal_load(G4 + GP * base + k) : v4u{0u, 0u, 0u, 0u};
-        }
+        if constexpr (WAVES == 1) load_dp();
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             const int k = 64 * q + lane;
@@ -2817,6 +2816,7 @@ __global__ __launch_bounds__(64 * kB8BwdWaves, 2) void implicit8_bwd_kernel(cons
             T[4 * r] = t.x; T[4 * r + 1] = t.y; T[4 * r + 2] = t.z; T[4 * r + 3] = t.w;
         }
         __builtin_amdgcn_wave_barrier();
+        if constexpr (WAVES > 1) load_dp();
         // dP stays in the tile (read twice below)
 #pragma unroll
         for (int q = 0; q < GP; ++q) {
@@ -3671,11 +3671,30 @@ int launch_bwd(Kernel kern, const float* P, const void* dP, void* dH, int64_t B,
     return launch_status();
 }
 
-template <typename Kernel>
-int launch_bwd8(Kernel kern, const float* P, const void* dP, void* dH, int64_t B, hipStream_t stream,
-                const float* a = nullptr, float eta = 1.f) {
-    launch_kernel(kern, dim3(static_cast<unsigned>(bwd_grid(B, kB8BwdWaves))), dim3(64 * kB8BwdWaves), 0, stream, P, dP, dH, B, a,
-                  eta);
+// One-wave or four-wave blocks, us at the sizes that a kernel's arrays stay in the last-level cache.
+// fp32 dH, fp32 dP / bf16 dP, four waves against one: 5 * 10^4 problems 9.9 and 9.6 / 9.4 and 9.0; 8 * 10^4
+// 12.1 and 13.0 / 10.9 and 11.1; 1.3 * 10^5 15.6 and 17.6 / 13.8 and 14.9; 1.6 * 10^5 24.1 and 24.9 / 21.7
+// and 22.3; 2 * 10^5 31.0 and 27.2 / 25.0 and 24.5 (a third block on half of the CUs); 2.5 * 10^5 34.8 and 35.4 /
+// 29.1 and 30.9; 2.7 * 10^5 38.2 and 36.2 / 33.5 and 31.6; 10^6 129 and 125 / 113 and 107. OT: 7 * 10^4 13.7 and 13.5,
+// 10^5 14.2 and 15.0, 1.1 * 10^5 15.2 and 15.9, 1.2 * 10^5 16.7 and 16.1, 2 * 10^5 32.6 and 29.0. bf16 dH keeps one
+// wave (bf16 dP, 10^5 10.5 and 10.4, 1.6 * 10^5 19.0 and 18.8).
+bool bwd8_four_waves(int64_t B, bool ot) {
+    constexpr int64_t u = 16384;
+    if (ot) return B > 5 * u && B <= 7 * u;
+    return B > 4 * u && B <= 16 * u && !(B > 12 * u && B <= 14 * u);
+}
+
+template <int DT, int DO, bool OT, bool IN_PLACE = false>
+int launch_bwd8(const float* P, const void* dP, void* dH, int64_t B, hipStream_t stream, const float* a = nullptr,
+                float eta = 1.f) {
+    if constexpr (DO == BIRKHOFF4_F32)
+        if (bwd8_four_waves(B, OT)) {
+            launch_kernel((implicit8_bwd_kernel<DT, DO, OT, IN_PLACE, 4>), dim3(static_cast<unsigned>(bwd_grid(B, 4))),
+                          dim3(256), 0, stream, P, dP, dH, B, a, eta);
+            return launch_status();
+        }
+    launch_kernel((implicit8_bwd_kernel<DT, DO, OT, IN_PLACE>), dim3(static_cast<unsigned>(bwd_grid(B, 1))), dim3(64), 0,
+                  stream, P, dP, dH, B, a, eta);
     return launch_status();
 }
 
@@ -3940,7 +3959,7 @@ int birkhoff8_ot_bwd(const float* T, const float* a, const float* dT, float eta,
     if (misaligned(T) || misaligned(a) || misaligned(dT) || misaligned(dM)) return BIRKHOFF4_ERR_ALIGN;
     const size_t nm = static_cast<size_t>(B) * 256, nv = static_cast<size_t>(B) * 32;
     if (overlaps(dM, nm, T, nm) || overlaps(dM, nm, dT, nm) || overlaps(dM, nm, a, nv)) return BIRKHOFF4_ERR_OVERLAP;
-    return launch_bwd8(implicit8_bwd_kernel<BIRKHOFF4_F32, BIRKHOFF4_F32, true>, T, dT, dM, B, stream, a, eta);
+    return launch_bwd8<BIRKHOFF4_F32, BIRKHOFF4_F32, true>(T, dT, dM, B, stream, a, eta);
 }
 
 int birkhoff8_fwd(const void* H, int h_dtype, float* P, float* dual, int32_t* iters, int64_t B, float tol,
@@ -3973,9 +3992,9 @@ int birkhoff8_bwd_ex(const float* P, const void* dP, int dp_dtype, void* dH, int
                  nh = static_cast<size_t>(B) * 64 * dtype_bytes(dh_dtype);
     if (overlaps(dH, nh, P, n) || overlaps(dH, nh, dP, ng)) return BIRKHOFF4_ERR_OVERLAP;
     constexpr int F = BIRKHOFF4_F32, H = BIRKHOFF4_BF16;
-    auto kern = dp_dtype == H ? (dh_dtype == H ? implicit8_bwd_kernel<H, H, false> : implicit8_bwd_kernel<H, F, false>)
-                              : (dh_dtype == H ? implicit8_bwd_kernel<F, H, false> : implicit8_bwd_kernel<F, F, false>);
-    return launch_bwd8(kern, P, dP, dH, B, stream);
+    if (dp_dtype == H)
+        return dh_dtype == H ? launch_bwd8<H, H, false>(P, dP, dH, B, stream) : launch_bwd8<H, F, false>(P, dP, dH, B, stream);
+    return dh_dtype == H ? launch_bwd8<F, H, false>(P, dP, dH, B, stream) : launch_bwd8<F, F, false>(P, dP, dH, B, stream);
 }
 
 int birkhoff8_bwd(const float* P, const void* dP, int dp_dtype, float* dH, int64_t B, hipStream_t stream) {
@@ -4189,9 +4208,8 @@ int birkhoff8_mix_bwd_ex(const float* P, const void* X, const void* dY, int x_dt
     const int e = x_dtype == H ? launch_mix_bwd<H, 8>(P, X, dY, dX, dP, false, B, nc, stream)
                                : launch_mix_bwd<F, 8>(P, X, dY, dX, dP, false, B, nc, stream);
     if (e) return e;
-    if (in_place) return launch_bwd8(implicit8_bwd_kernel<F, F, false, true>, P, dP, dH, B, stream);
-    return launch_bwd8(dh_dtype == H ? implicit8_bwd_kernel<F, H, false> : implicit8_bwd_kernel<F, F, false>, P, dP, dH,
-                       B, stream);
+    if (in_place) return launch_bwd8<F, F, false, true>(P, dP, dH, B, stream);
+    return dh_dtype == H ? launch_bwd8<F, H, false>(P, dP, dH, B, stream) : launch_bwd8<F, F, false>(P, dP, dH, B, stream);
 }
 
 int birkhoff8_mix_bwd(const float* P, const void* X, const void* dY, int x_dtype, void* dX, float* dH, int64_t B,

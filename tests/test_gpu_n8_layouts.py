@@ -7,7 +7,7 @@ import torch
 
 import paper_2606_07574_amd as b4
 from oracle import birkhoffn as on
-from tests._gpu import say, to_dev
+from tests._gpu import TOL_DH, say, to_dev
 from tests.test_gpu_n8 import check, gauss8, near_perm8
 from tests.test_gpu_ot8 import check as check_ot, problem
 
@@ -75,3 +75,50 @@ def test_ot_layouts(B):
     assert (it >= 0).all()
     check_ot(M, a, b, 0.5, T[:n].cpu().numpy(), dual[:n].cpu().numpy(), label=f"B={B}")
     assert copies_agree(T, n) and copies_agree(dual, n)
+
+
+# fp32 dH: blocks of four waves from 65537 problems to 262144 but for the quarter after 196608 (OT:
+# from 81921 to 114688), one-wave blocks elsewhere
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B", [65536, 65537, 131072 + 63, 196608, 196609, 229376, 229377, 262144, 262145])
+def test_backward_layouts(dtype, B):
+    say(f"test: 8x8 backward layouts, dP {dtype}, B={B}")
+    H, dP = gauss8(1501, 5.0, 17)
+    n = H.shape[0]
+    P = b4.fwd8(to_dev(H), want_dual=False)[0]
+    dPd = to_dev(dP, dtype)
+    ref = on.bwd(P.double().cpu().numpy(), dPd.double().cpu().numpy())
+    out = torch.full((B + 1, 8, 8), 3.0, device="cuda:0")  # the last matrix is not written
+    dH = b4.bwd8(tiled(P, B), tiled(dPd, B), out=out[:B])
+    e = np.abs(dH[:n].cpu().numpy() - ref).max(axis=(1, 2)) / np.maximum(1.0, np.abs(ref).max(axis=(1, 2)))
+    assert e.max() <= TOL_DH
+    assert copies_agree(dH, n) and (out[B] == 3.0).all()
+
+
+@pytest.mark.parametrize("B", [81920, 81921, 98304 + 1, 114688, 114689])
+def test_ot_backward_layouts(B):
+    say(f"test: 8x8 OT backward layouts, B={B}")
+    M, a, b, G = problem(1501, 2.0, 19)
+    n = M.shape[0]
+    T = b4.ot8_fwd(*(to_dev(x) for x in (M, a, b)), 0.5, want_dual=False)[0]
+    dM = b4.ot8_bwd(tiled(T, B), tiled(to_dev(a), B), tiled(to_dev(G), B), 0.5)
+    ref = on.ot_bwd(T.double().cpu().numpy(), a.astype(np.float64), G.astype(np.float64), 0.5)
+    e = np.abs(dM[:n].cpu().numpy() - ref).max(axis=(1, 2)) / np.maximum(1.0, np.abs(ref).max(axis=(1, 2)))
+    assert e.max() <= TOL_DH
+    assert copies_agree(dM, n)
+
+
+@pytest.mark.parametrize("B", [65537, 196609])
+def test_mixing_backward_layouts(B):
+    """dP turned into dH in its own memory: as the backward of the separately computed dP."""
+    say(f"test: 8x8 backward in place, B={B}")
+    H = gauss8(601, 5.0, 23)[0]
+    P = tiled(b4.fwd8(to_dev(H), want_dual=False)[0], B)
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(B)
+    X, dY = (torch.randn(B, 8, 4, device="cuda:0", generator=g) for _ in range(2))
+    _, dH = b4.mix8_bwd(P, X, dY)
+    dP = (dY.double().unsqueeze(2) * X.double().unsqueeze(1)).sum(-1)
+    ref = b4.bwd8(P, dP.float())
+    scale = torch.clamp(ref.abs().amax((1, 2)), min=1.0)
+    assert ((dH - ref).abs().amax((1, 2)) / scale).max() <= 2 * TOL_DH  # two gradients within TOL_DH of the exact one
