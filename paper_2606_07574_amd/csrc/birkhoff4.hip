@@ -1585,12 +1585,17 @@ __global__ __launch_bounds__(kSkBlock) void sk_fwd_kernel(const void* __restrict
 }
 
 // One problem per lane: where the steps of a large batch outweigh its loads and stores this
-// has a little less to issue than the quads (no wait states). 2^20 problems fp32, this / quads in
-// us: 10 steps 32.0 / 24.0, 20 steps 36.8 / 38.9, 30 steps 49.1 / 54.8; 2 * 10^5: 20 steps 11.7 /
-// 10.6; 5000: 20 steps 4.7 / 3.1.
-constexpr int64_t kSkLaneMinB = int64_t(1) << 19;
-constexpr int kSkLaneMinSteps = 16;
-
+// has a little less to issue than the quads (no wait states). us, quads / this: fp32, 2^20
+// problems 8 steps 20.4 / 28.6, 12 27.6 / 29.1, 13 30.2 / 28.8, 20 38.9 / 36.8, 30 54.8 / 49.1; 2 * 10^5,
+// 20 steps 10.6 / 11.7; 5000, 20 steps 3.1 / 4.7. The line (sk_lanes) is lower for bf16 logits, whose
+// loads weigh less, and for many steps; share of this kernel's time that the quads take:
+//               12 steps    13          16          20          48
+//    2^18  fp32 0.92        0.93        0.94        0.96        1.00
+//    2^18  bf16 0.93        0.95        0.97        0.98        1.01
+//    393 K fp32 0.95        0.99        0.99        1.01        1.03
+//    393 K bf16 1.01        1.02        1.03        1.03        1.06
+//    2^19  fp32 0.89        0.95        1.01        1.02        1.04
+//    2^20  bf16 1.08        1.08        1.09        1.08        1.08
 template <int DT>
 __global__ __launch_bounds__(kSkBlock) void sk_fwd_lane_kernel(const void* __restrict__ H, float* __restrict__ P,
                                                                int64_t B, int n_steps) {
@@ -3698,6 +3703,12 @@ int launch_bwd8(const float* P, const void* dP, void* dH, int64_t B, hipStream_t
     return launch_status();
 }
 
+// Sinkhorn forward: one problem per lane, or four lanes per problem (see sk_fwd_lane_kernel).
+bool sk_lanes(int64_t B, int n_steps, bool h16) {
+    if (n_steps >= 32 && B >= int64_t(1) << 18) return true;
+    return h16 ? n_steps >= 12 && B >= int64_t(11) << 15 : n_steps >= 13 && B >= int64_t(31) << 14;
+}
+
 constexpr int kSkGridPerCu = 256;  // blocks per CU of the Sinkhorn kernels' grid; further problems loop
 
 // Residual mixing: block and grid. A row is `cols` columns of 64 chunks, one per wave, up to
@@ -4054,7 +4065,7 @@ int birkhoff4_sk_fwd(const void* H, int h_dtype, float* P, int64_t B, int n_step
         return BIRKHOFF4_ERR_OVERLAP;
     int cus = 0, dev = 0;
     if (int e = device_cus(stream, &cus, &dev)) return e;
-    const bool h16 = h_dtype == BIRKHOFF4_BF16, lanes = B >= kSkLaneMinB && n_steps >= kSkLaneMinSteps;
+    const bool h16 = h_dtype == BIRKHOFF4_BF16, lanes = sk_lanes(B, n_steps, h16);
     const int64_t grid = lanes ? grid_for(B, kSkBlock, cus, 64) : grid_for(B, kSkBlock / 4, cus, kSkGridPerCu);
     auto kern = lanes ? (h16 ? sk_fwd_lane_kernel<BIRKHOFF4_BF16> : sk_fwd_lane_kernel<BIRKHOFF4_F32>)
                       : (h16 ? sk_fwd_kernel<BIRKHOFF4_BF16> : sk_fwd_kernel<BIRKHOFF4_F32>);

@@ -40,13 +40,20 @@ def test_ragged(B, steps):
     check(workloads.bf16_to_f32(Hb), workloads.bf16_to_f32(Gb), bits_to_dev(Hb), bits_to_dev(Gb), steps, "bf16")
 
 
-@pytest.mark.parametrize("steps", [15, 16, 20])
-@pytest.mark.parametrize("B", [(1 << 19) - 1, 1 << 19, (1 << 19) + 77])
-def test_large(B, steps):
-    say(f"test: Sinkhorn layouts, B={B}, {steps} steps")
+# lines of the forward's layouts: fp32 13 steps and 31 * 2^14 problems, bf16 12 steps and 11 * 2^15,
+# from 32 steps on 2^18
+@pytest.mark.parametrize("dtype,steps,B", [(d, s, b) for d, steps, line in ((torch.float32, (12, 13, 20), 31 << 14),
+                                                                            (torch.bfloat16, (11, 12, 20), 11 << 15))
+                                           for s in steps for b in (line - 1, line)]
+                         + [(d, s, b) for d in (torch.float32, torch.bfloat16) for s in (31, 32)
+                            for b in ((1 << 18) - 1, 1 << 18)] + [(torch.float32, 20, (1 << 19) + 77)])
+def test_large(dtype, B, steps):
+    say(f"test: Sinkhorn layouts, {dtype}, B={B}, {steps} steps")
     H, dP = workloads.gauss(5003, 3.0, seed=steps)
+    if dtype == torch.bfloat16:
+        H, dP = (workloads.bf16_to_f32(workloads.bf16_bits(x)) for x in (H, dP))
     k = -(-B // 5003)
-    Hd, dPd = (torch.cat([to_dev(x)] * k)[:B].contiguous() for x in (H, dP))
+    Hd, dPd = (torch.cat([to_dev(x, dtype)] * k)[:B].contiguous() for x in (H, dP))
     P, dH = check(H, dP, Hd, dPd, steps, f"B={B} n={steps}")
     for i in range(5003, B, 5003):  # every copy of the problems gives the same bits
         m = min(5003, B - i)
