@@ -1670,14 +1670,17 @@ __device__ __forceinline__ void sk_store(float* __restrict__ dH, int64_t b, int 
     reinterpret_cast<v4f*>(dH)[4 * b + q] = v4f{d.Ab[0] * A[0], d.Ab[1] * A[1], d.Ab[2] * A[2], d.Ab[3] * A[3]};
 }
 
-// Any number of steps: the iterates are kept in LDS (blocks of one wave, [k][lane]).
+// Any number of steps: the iterates are kept in LDS (blocks of one wave, [k][lane]), both of them
+// or, in half the LDS, the v^(k) alone, from which the sweep computes each u^(k) again.
 constexpr int kSkLdsBlock = 64;
 
-template <int DT, int DG>
+template <int DT, int DG, bool KEEP_U>
 __global__ __launch_bounds__(kSkLdsBlock) void sk_bwd_kernel(const void* __restrict__ H, const void* __restrict__ dP,
                                                              float* __restrict__ dH, int64_t B, int n_steps) {
-    extern __shared__ float iter[];  // u^(k) at [2 k - 2][64], v^(k) at [2 k - 1][64]
+    // KEEP_U: u^(k) at [2 k - 2][64], v^(k) at [2 k - 1][64]; else v^(k) at [k - 1][64]
+    extern __shared__ float iter[];
     const int lane = threadIdx.x, q = lane & 3;
+    auto vat = [&](int k) -> float& { return iter[(KEEP_U ? 2 * k - 1 : k - 1) * kSkLdsBlock + lane]; };
     const int64_t stride = static_cast<int64_t>(gridDim.x) * (kSkLdsBlock / 4);
     for (int64_t b = static_cast<int64_t>(blockIdx.x) * (kSkLdsBlock / 4) + (lane >> 2); b < B; b += stride) {
         float h[4], G[4], A[4], Ac[4], u = 0.f, v = 1.f;
@@ -1687,15 +1690,17 @@ __global__ __launch_bounds__(kSkLdsBlock) void sk_bwd_kernel(const void* __restr
         for (int k = 1; k <= n_steps; ++k) {
             u = sk_rcp(qdot(A, v));
             v = sk_rcp(qdot(Ac, u));
-            iter[(2 * k - 2) * kSkLdsBlock + lane] = u;
-            iter[(2 * k - 1) * kSkLdsBlock + lane] = v;
+            if constexpr (KEEP_U) iter[(2 * k - 2) * kSkLdsBlock + lane] = u;
+            vat(k) = v;
         }
         SkAdjoint d = sk_adjoint_init(A, G, u, v, q);
         for (int k = n_steps; k >= 1; --k) {
-            const float vp = k > 1 ? iter[(2 * k - 3) * kSkLdsBlock + lane] : 1.f;
+            const float vp = k > 1 ? vat(k - 1) : 1.f;
+            if constexpr (!KEEP_U) u = sk_rcp(qdot(A, vp));
             sk_reverse(A, Ac, u, v, vp, k == n_steps, d);
             v = vp;
-            if (k > 1) u = iter[(2 * k - 4) * kSkLdsBlock + lane];
+            if constexpr (KEEP_U)
+                if (k > 1) u = iter[(2 * k - 4) * kSkLdsBlock + lane];
         }
         sk_store(dH, b, q, d, A);
     }
@@ -3709,6 +3714,19 @@ bool sk_lanes(int64_t B, int n_steps, bool h16) {
     return h16 ? n_steps >= 12 && B >= int64_t(11) << 15 : n_steps >= 13 && B >= int64_t(31) << 14;
 }
 
+// Sinkhorn backward in LDS: whether the u^(k) are kept too. Their LDS sets how many waves a CU
+// holds; kept is 5-15 % faster while the batch fits in one round of them or the steps are so few
+// that LDS does not limit the waves, and slower where it takes a second round. us, kept / computed
+// again: 65536 problems, 30 steps (10 waves a CU, 16 needed) 18.3 / 14.7, 18 steps 10.9 / 12.0; 131072, 16
+// steps (20, 32 needed) 16.8 / 14.9, 10 steps 9.9 / 10.8; 2^20, 12 steps 65.1 / 71.0, 16 83.0 / 83.8,
+// 18 94.0 / 92.5, 30 166 / 149.
+bool sk_keep_u(int64_t B, int n_steps, int cus) {
+    constexpr int kLds = 160 * 1024;
+    const int64_t fit = kLds / (2 * n_steps * kSkLdsBlock * static_cast<int>(sizeof(float)));  // waves per CU
+    const int64_t need = ((B + 15) / 16 + cus - 1) / cus;
+    return need <= fit || n_steps <= 11 || (n_steps <= 16 && need > 4 * fit);
+}
+
 constexpr int kSkGridPerCu = 256;  // blocks per CU of the Sinkhorn kernels' grid; further problems loop
 
 // Residual mixing: block and grid. A row is `cols` columns of 64 chunks, one per wave, up to
@@ -4096,8 +4114,12 @@ int birkhoff4_sk_bwd(const void* H, int h_dtype, const void* dP, int dp_dtype, f
                       stream, H, dP, dH, B);
         return launch_status();
     }
-    auto kern = h16 ? (g16 ? sk_bwd_kernel<X, X> : sk_bwd_kernel<X, F>) : (g16 ? sk_bwd_kernel<F, X> : sk_bwd_kernel<F, F>);
-    const unsigned lds = static_cast<unsigned>(2 * n_steps * kSkLdsBlock * sizeof(float));
+    const bool u = sk_keep_u(B, n_steps, cus);
+    auto kern = h16 ? (g16 ? (u ? sk_bwd_kernel<X, X, true> : sk_bwd_kernel<X, X, false>)
+                           : (u ? sk_bwd_kernel<X, F, true> : sk_bwd_kernel<X, F, false>))
+                    : (g16 ? (u ? sk_bwd_kernel<F, X, true> : sk_bwd_kernel<F, X, false>)
+                           : (u ? sk_bwd_kernel<F, F, true> : sk_bwd_kernel<F, F, false>));
+    const unsigned lds = static_cast<unsigned>((u ? 2 : 1) * n_steps * kSkLdsBlock * sizeof(float));
     launch_kernel(kern, dim3(static_cast<unsigned>(grid_for(B, kSkLdsBlock / 4, cus, 4 * kSkGridPerCu))),
                   dim3(kSkLdsBlock), lds, stream, H, dP, dH, B, n_steps);
     return launch_status();

@@ -58,3 +58,19 @@ def test_large(dtype, B, steps):
     for i in range(5003, B, 5003):  # every copy of the problems gives the same bits
         m = min(5003, B - i)
         assert torch.equal(P[i:i + m], P[:m]) and torch.equal(dH[i:i + m], dH[:m])
+
+
+# backward with the iterates in LDS: 160 KB hold 512 n bytes per wave of 16 problems with both
+# iterates; a batch that 256 CUs do not hold at once keeps the v^(k) alone (16 steps: up to four
+# rounds of waves; 11 and fewer: never)
+@pytest.mark.parametrize("steps,B", [(11, 4096 * 28 + 1), (12, 4096 * 26), (12, 4096 * 26 + 1), (16, 4096 * 80),
+                                     (16, 4096 * 80 + 1), (33, 4096 * 9), (33, 4096 * 9 + 1), (48, 4096 * 6 + 77)])
+def test_backward_in_lds(steps, B):
+    say(f"test: Sinkhorn backward in LDS, B={B}, {steps} steps")
+    H, dP = workloads.gauss(2003, 3.0, seed=steps)
+    k = -(-B // 2003)
+    Hd, dPd = (torch.cat([to_dev(x)] * k)[:B].contiguous() for x in (H, dP))
+    _, dH = check(H, dP, Hd, dPd, steps, f"B={B} n={steps}")
+    small = b4.sk_bwd(Hd[:2003], dPd[:2003], steps)  # both iterates kept
+    for i in range(0, B, 2003):
+        assert torch.equal(dH[i:i + 2003], small[:min(2003, B - i)])
