@@ -1417,7 +1417,9 @@ __global__ __launch_bounds__(64 * mix_bwd_max_waves(N)) void mix_bwd_kernel(cons
 // Short rows, nc <= L with L = 8, 16 or 32: L lanes per token, 64 / L tokens per wave, one
 // chunk of every row per lane, P read per lane. A wave of its own for each token would leave
 // most lanes idle: 3 * 10^4 tokens of 4 x 128 bf16 channels forward 14.9 -> 11.5 us, backward 56.2 -> 17.3.
-constexpr int kMixShortBlock = 256;
+// Blocks of 256 threads; of 64 with 16 lanes per token, four to a block, so that a few thousand
+// tokens reach every CU (4097 tokens of 4 x 64 fp32 channels forward 13.0 -> 12.0 us with the projection).
+constexpr int mix_short_block(int lanes) { return lanes == 16 ? 64 : 256; }
 
 template <int N>
 __device__ __forceinline__ void load_lane_matrix(const float* __restrict__ P, int64_t t, float p[N * N]) {
@@ -1430,12 +1432,13 @@ __device__ __forceinline__ void load_lane_matrix(const float* __restrict__ P, in
 }
 
 template <int DX, int N, int L>
-__global__ __launch_bounds__(kMixShortBlock) void mix_fwd_short_kernel(const float* __restrict__ P,
-                                                                       const v4u* __restrict__ X, v4u* __restrict__ Y,
-                                                                       int64_t B, int nc) {
+__global__ __launch_bounds__(mix_short_block(L)) void mix_fwd_short_kernel(const float* __restrict__ P,
+                                                                           const v4u* __restrict__ X,
+                                                                           v4u* __restrict__ Y, int64_t B, int nc) {
+    constexpr int T = mix_short_block(L) / L;  // tokens per block
     const int c = threadIdx.x % L;
-    for (int64_t t = static_cast<int64_t>(blockIdx.x) * (kMixShortBlock / L) + threadIdx.x / L; t < B;
-         t += static_cast<int64_t>(gridDim.x) * (kMixShortBlock / L)) {
+    for (int64_t t = static_cast<int64_t>(blockIdx.x) * T + threadIdx.x / L; t < B;
+         t += static_cast<int64_t>(gridDim.x) * T) {
         if (c >= nc) return;
         const int64_t off = static_cast<int64_t>(N) * nc * t + c;
         v4u x[N], y[N];
@@ -1450,15 +1453,15 @@ __global__ __launch_bounds__(kMixShortBlock) void mix_fwd_short_kernel(const flo
 }
 
 template <int DX, int N, int L>
-__global__ __launch_bounds__(kMixShortBlock) void mix_bwd_short_kernel(const float* __restrict__ P,
-                                                                       const v4u* __restrict__ X,
-                                                                       const v4u* __restrict__ dY,
-                                                                       v4u* __restrict__ dX, void* __restrict__ dH,
-                                                                       int64_t B, int nc, bool h16) {
-    constexpr int NN = N * N;
+__global__ __launch_bounds__(mix_short_block(L)) void mix_bwd_short_kernel(const float* __restrict__ P,
+                                                                           const v4u* __restrict__ X,
+                                                                           const v4u* __restrict__ dY,
+                                                                           v4u* __restrict__ dX, void* __restrict__ dH,
+                                                                           int64_t B, int nc, bool h16) {
+    constexpr int NN = N * N, T = mix_short_block(L) / L;  // T: tokens per block
     const int c = threadIdx.x % L;
-    const int64_t first = static_cast<int64_t>(blockIdx.x) * (kMixShortBlock / L);
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * (kMixShortBlock / L);
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * T;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * T;
     for (int64_t base = first; base < B; base += stride) {  // uniform over the block: every lane takes part in the sums
         const int64_t t = base + threadIdx.x / L;
         const bool valid = t < B, own = valid && c < nc;
@@ -3742,8 +3745,9 @@ constexpr int kSkGridPerCu = 256;  // blocks per CU of the Sinkhorn kernels' gri
 //  * n = 8 backward, up to 4: its registers leave two waves per SIMD, so a larger block leaves a
 //    CU with one: 2^14 tokens of 8 x 4096 514 with 4 waves, 608 with 8; 16000 of 8 x 2560 (5
 //    columns) 348 with 3, 500 with 5.
-//  * One column per row: in the forward four tokens share a block (two with n = 8): 3 * 10^4
-//    tokens of 4 x 504 40.2, alone 41.3; in the backward they don't: 58.3, shared 61.3.
+//  * In the forward four tokens share a block of one column per row (two with n = 8): 3 * 10^4 tokens
+//    of 4 x 504 40.2, alone 41.3; with n = 4 of two columns too: 2 * 10^4 tokens of 4 x 520 46.6, alone
+//    48.6. In the backward they don't: 58.3, shared 61.3.
 //  * XCD windows of 16 tokens: 2^15 tokens of 4 x 4096 forward 384 -> 344 and backward 536 ->
 //    517, 2^14 of 8 x 4096 forward 365 -> 346; none for the n = 8 backward and wide n = 8 rows (8 x
 //    4096 fp32 backward 522, with windows 557).
@@ -3759,11 +3763,12 @@ struct MixLaunch {
 MixLaunch mix_launch(int64_t B, int64_t nc, int n, bool backward) {
     const int64_t cols = nc > 0 ? (nc + 63) / 64 : 1;
     const bool wide8 = n == 8 && cols > 8;
-    const bool whole = !backward || (cols > 14 && cols <= kMixMaxWaves);
-    const int64_t most = n == 4 ? (whole ? kMixMaxWaves : 8) : (backward || wide8 ? 4 : 8);
+    int64_t most = n == 4 ? kMixMaxWaves : wide8 ? 4 : 8;
+    if (backward && n == 4) most = cols > 14 && cols <= kMixMaxWaves ? kMixMaxWaves : 8;
+    if (backward && n == 8) most = 4;
     const int64_t turns = (cols + most - 1) / most;
     const int64_t waves = (cols + turns - 1) / turns;
-    const unsigned tokens = waves > 1 || backward ? 1 : n == 4 ? 4 : 2;
+    const unsigned tokens = backward || waves > (n == 4 ? 2 : 1) ? 1 : n == 4 ? 4 : 2;
     const int64_t count = (B + tokens - 1) / tokens;
     const int64_t shares = backward ? 1 : (turns < kMixMaxShares ? turns : kMixMaxShares);
     return {dim3(static_cast<unsigned>(count < kMixMaxGrid ? count : kMixMaxGrid), static_cast<unsigned>(shares)),
@@ -3771,7 +3776,7 @@ MixLaunch mix_launch(int64_t B, int64_t nc, int n, bool backward) {
 }
 
 unsigned mix_short_grid(int64_t B, int lanes) {
-    const int64_t per = kMixShortBlock / lanes, want = (B + per - 1) / per;
+    const int64_t per = mix_short_block(lanes) / lanes, want = (B + per - 1) / per;
     return static_cast<unsigned>(want < kMixMaxGrid ? want : kMixMaxGrid);
 }
 
@@ -3779,14 +3784,17 @@ template <int DX, int N = 4>
 int launch_mix_fwd(const float* P, const void* X, void* Y, int64_t B, int64_t nc, hipStream_t stream) {
     const v4u* x = static_cast<const v4u*>(X);
     v4u* y = static_cast<v4u*>(Y);
-    // (the 64 entries of P that each lane of an 8-stream token reads cost more than idle lanes
-    // once only two tokens share a wave: 3 * 10^4 tokens of 32 chunks 62 us, a wave each 46 us)
-    if (nc <= (N == 4 ? kMixShortRow : 16)) {
+    // (The 64 entries of P that each lane of an 8-stream token reads cost more than idle lanes
+    // once only two tokens share a wave: 3 * 10^4 tokens of 32 chunks 62 us, a wave each 46 us. So do the
+    // 16 of a 4-stream token with fp32, whose mixing is half as much work: 2 * 10^4 tokens of 17
+    // chunks with the projection 21.2, a wave each 19.4; bf16 the same both ways.)
+    constexpr int64_t kShort = N == 4 && DX == BIRKHOFF4_BF16 ? kMixShortRow : 16;
+    if (nc <= kShort) {
         const int L = nc <= 8 ? 8 : nc <= 16 ? 16 : 32;
         auto kern = L == 8 ? mix_fwd_short_kernel<DX, N, 8> : mix_fwd_short_kernel<DX, N, 16>;
-        if constexpr (N == 4)
+        if constexpr (kShort > 16)
             if (L == 32) kern = mix_fwd_short_kernel<DX, N, 32>;
-        launch_kernel(kern, dim3(mix_short_grid(B, L)), dim3(kMixShortBlock), 0, stream, P, x, y, B,
+        launch_kernel(kern, dim3(mix_short_grid(B, L)), dim3(mix_short_block(L)), 0, stream, P, x, y, B,
                       static_cast<int>(nc));
         return launch_status();
     }
@@ -3837,7 +3845,7 @@ int launch_mix_bwd(const float* P, const void* X, const void* dY, void* dX, void
         const int L = nc <= 8 ? 8 : nc <= 16 ? 16 : 32;
         auto kern = L == 8 ? mix_bwd_short_kernel<DX, N, 8>
                            : L == 16 ? mix_bwd_short_kernel<DX, N, 16> : mix_bwd_short_kernel<DX, N, 32>;
-        launch_kernel(kern, dim3(mix_short_grid(B, L)), dim3(kMixShortBlock), 0, stream, P, x, dy, dx, dH, B,
+        launch_kernel(kern, dim3(mix_short_grid(B, L)), dim3(mix_short_block(L)), 0, stream, P, x, dy, dx, dH, B,
                       static_cast<int>(nc), h16);
         return launch_status();
     }

@@ -6,7 +6,7 @@ import torch
 
 import paper_2606_07574_amd as b4
 import workloads
-from tests._gpu import say
+from tests._gpu import TOL_DH, say
 from tests.test_gpu_mix import check_case
 from tests.test_gpu_n8 import gauss8
 
@@ -66,3 +66,40 @@ def test_fused_call_outputs(n, h_dtype):
                 ok = torch.isfinite(ref)
                 assert (torch.isfinite(Y) == ok).all()
                 assert ((Y.double() - ref)[ok].abs() <= 1e-5 * X.abs().max()).all()
+
+
+# rows of one and two columns with four tokens to a block (n = 4), short rows with fp32
+TOKEN_LINES = [(n, d, nc, B) for d in (torch.bfloat16, torch.float32)
+               for n, nc, B in [(4, 17, 4099), (4, 128, 4101), (4, 129, 4101)]]
+
+
+@pytest.mark.parametrize("n,dtype,nc,B", TOKEN_LINES, ids=[f"{n}-{str(d)[6:]}-{c}x{b}" for n, d, c, b in TOKEN_LINES])
+def test_token_lines(n, dtype, nc, B):
+    """Every token of the batch against a float64 product on the GPU; the projection and its
+    backward, which the other tests hold to the oracle, on the same P."""
+    C = nc * (8 if dtype == torch.bfloat16 else 4)
+    say(f"test: mixing layouts by token count, n={n} {dtype} C={C} ({nc} chunks), B={B}")
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(nc + B)
+    H = 3.0 * torch.randn(B, n, n, device="cuda:0", generator=g)
+    X, dY = (torch.randn(B, n, C, device="cuda:0", generator=g).to(dtype) for _ in range(2))
+    mfwd, mbwd, bwd = (b4.mix_fwd, b4.mix_bwd, b4.bwd) if n == 4 else (b4.mix8_fwd, b4.mix8_bwd, b4.bwd8)
+    Y, P, _, _ = mfwd(H, X)
+    dX, dH = mbwd(P, X, dY)
+    dP = torch.empty(B, n, n, dtype=torch.float64, device="cuda:0")
+    for i in range(n):
+        y = sum(P[:, i, j, None].double() * X[:, j].double() for j in range(n))
+        s = X.float().abs().sum(1)
+        # fp32 sums of n products of |P| <= 1: (n + 1) 2^-24 of the sum of the magnitudes; bf16 results
+        # rounded once more (2^-8, as half a unit in the last place is at most that of the value)
+        tol = (n + 1) * 2.0 ** -24 * s + (2.0 ** -8 * y.abs() if dtype == torch.bfloat16 else 0) + 1e-30
+        assert ((Y[:, i].double() - y).abs() <= tol).all()
+        x = sum(P[:, j, i, None].double() * dY[:, j].double() for j in range(n))
+        s = dY.float().abs().sum(1)
+        tol = (n + 1) * 2.0 ** -24 * s + (2.0 ** -8 * x.abs() if dtype == torch.bfloat16 else 0) + 1e-30
+        assert ((dX[:, i].double() - x).abs() <= tol).all()
+        for j in range(n):
+            dP[:, i, j] = (dY[:, i].double() * X[:, j].double()).sum(1)
+    ref = bwd(P, dP.float())
+    scale = torch.clamp(ref.abs().amax((1, 2)), min=1.0)
+    assert ((dH - ref).abs().amax((1, 2)) / scale).max() <= 2 * TOL_DH  # each within TOL_DH of the exact gradient
