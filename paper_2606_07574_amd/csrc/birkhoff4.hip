@@ -3737,9 +3737,12 @@ constexpr int kSkGridPerCu = 256;  // blocks per CU of the Sinkhorn kernels' gri
 // turns of the block's waves (backward). Measured lines (us, bf16 unless said):
 //  * n = 4 forward, up to 16 waves: 2 * 10^4 tokens of 4 x 6144 (12 columns) 317 with 12 waves,
 //    360 with 6, 351 with 4; 2^14 tokens of 4 x 4096 fp32 (16) 341 with 16, 367 with 8.
-//  * n = 4 backward, up to 8, and 15 or 16 columns whole: 2 * 10^4 tokens of 4 x 4608 (9 columns)
-//    359 in two turns, 395 with 9 waves; 4 x 5632 431 and 466; 4 x 7168 (14) 557 and 571; 4 x
-//    7680 622 and 602; 4 x 8192 634 and 641; 2^14 tokens of 4 x 4096 fp32 (16) 530 and 498.
+//  * n = 4 backward, up to 8: 2 * 10^4 tokens of 4 x 4608 (9 columns) 359 in two turns, 395 with 9
+//    waves; 4 x 5632 431 and 466; 4 x 7168 (14) 557 and 571. 15 and 16 columns whole where that
+//    wins, share of the two turns' time: fp32 0.93-0.96 from 2^13 tokens (1.03 at 2^11 to 2^12 tokens of
+//    16 columns); up to 256 tokens, whose blocks are alone on a CU, 0.92-0.98; bf16 of 15 columns,
+//    which leave a wave idle in the second turn, 0.97 from 2^13 tokens (2^10: 1.08); bf16 of 16 columns
+//    1.02-1.09 from 300 tokens on: in turns.
 //  * n = 8 forward, up to 8 columns; wider rows in blocks of 4: 10^4 tokens of 8 x 6144 365 with
 //    4 waves, 376 with 6; 2^13 of 8 x 4096 fp32 366 with 4, 374 with 8.
 //  * n = 8 backward, up to 4: its registers leave two waves per SIMD, so a larger block leaves a
@@ -3760,11 +3763,14 @@ struct MixLaunch {
     int win;  // tokens in an XCD's window
 };
 
-MixLaunch mix_launch(int64_t B, int64_t nc, int n, bool backward) {
+MixLaunch mix_launch(int64_t B, int64_t nc, int n, bool backward, bool bf16) {
     const int64_t cols = nc > 0 ? (nc + 63) / 64 : 1;
-    const bool wide8 = n == 8 && cols > 8;
+    const bool wide8 = n == 8 && cols > 8, alone = B <= 256;  // alone: no second block on a CU
     int64_t most = n == 4 ? kMixMaxWaves : wide8 ? 4 : 8;
-    if (backward && n == 4) most = cols > 14 && cols <= kMixMaxWaves ? kMixMaxWaves : 8;
+    if (backward && n == 4) {
+        const bool whole = cols > 14 && cols <= kMixMaxWaves && (!bf16 || alone || (cols == 15 && B >= 8192));
+        most = whole ? kMixMaxWaves : 8;
+    }
     if (backward && n == 8) most = 4;
     const int64_t turns = (cols + most - 1) / most;
     const int64_t waves = (cols + turns - 1) / turns;
@@ -3798,7 +3804,7 @@ int launch_mix_fwd(const float* P, const void* X, void* Y, int64_t B, int64_t nc
                       static_cast<int>(nc));
         return launch_status();
     }
-    const MixLaunch l = mix_launch(B, nc, N, false);
+    const MixLaunch l = mix_launch(B, nc, N, false, DX == BIRKHOFF4_BF16);
     launch_kernel((mix_fwd_kernel<DX, N>), l.grid, l.block, 0, stream, P, x, y, B, nc, l.win);
     return launch_status();
 }
@@ -3849,7 +3855,7 @@ int launch_mix_bwd(const float* P, const void* X, const void* dY, void* dX, void
                       static_cast<int>(nc), h16);
         return launch_status();
     }
-    const MixLaunch l = mix_launch(B, nc, N, true);
+    const MixLaunch l = mix_launch(B, nc, N, true, DX == BIRKHOFF4_BF16);
     launch_kernel((mix_bwd_kernel<DX, N>), l.grid, l.block, 0, stream, P, x, dy, dx, dH, B, nc, l.win, h16);
     return launch_status();
 }

@@ -68,9 +68,11 @@ def test_fused_call_outputs(n, h_dtype):
                 assert ((Y.double() - ref)[ok].abs() <= 1e-5 * X.abs().max()).all()
 
 
-# rows of one and two columns with four tokens to a block (n = 4), short rows with fp32
+# lines that depend on the token count: up to 256 tokens and from 8192 tokens of 15 columns on, 15 and 16
+# columns whole with n = 4
 TOKEN_LINES = [(n, d, nc, B) for d in (torch.bfloat16, torch.float32)
-               for n, nc, B in [(4, 17, 4099), (4, 128, 4101), (4, 129, 4101)]]
+               for n, nc, B in [(4, 960, 256), (4, 960, 257), (4, 1024, 256), (4, 1024, 257), (4, 897, 8191),
+                                (4, 897, 8192), (4, 17, 4099), (4, 128, 4101), (4, 129, 4101)]]
 
 
 @pytest.mark.parametrize("n,dtype,nc,B", TOKEN_LINES, ids=[f"{n}-{str(d)[6:]}-{c}x{b}" for n, d, c, b in TOKEN_LINES])
