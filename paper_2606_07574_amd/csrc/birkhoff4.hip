@@ -1343,7 +1343,7 @@ __device__ __forceinline__ void store_dh_row(void* dH, bool h16, int64_t t, int 
 // sums its lanes' parts; with W > 1 the waves leave them in LDS and the first one adds them
 // in wave order, so the result does not depend on timing. For n = 4 it then forms dH; for n =
 // 8 it writes dP, lane L entry L, for the 8 x 8 backward to take over.
-constexpr int mix_bwd_max_waves(int n) { return n == 8 ? 4 : kMixMaxWaves; }
+constexpr int mix_bwd_max_waves(int n) { return n == 8 ? 8 : kMixMaxWaves; }
 
 template <int DX, int N>
 __global__ __launch_bounds__(64 * mix_bwd_max_waves(N)) void mix_bwd_kernel(const float* __restrict__ P,
@@ -3747,7 +3747,11 @@ constexpr int kSkGridPerCu = 256;  // blocks per CU of the Sinkhorn kernels' gri
 //    4 waves, 376 with 6; 2^13 of 8 x 4096 fp32 366 with 4, 374 with 8.
 //  * n = 8 backward, up to 4: its registers leave two waves per SIMD, so a larger block leaves a
 //    CU with one: 2^14 tokens of 8 x 4096 514 with 4 waves, 608 with 8; 16000 of 8 x 2560 (5
-//    columns) 348 with 3, 500 with 5.
+//    columns) 348 with 3, 500 with 5. Up to 256 tokens, one block per CU, 8: 96 tokens of 8 x
+//    16384 34.8 with 4, 30.8 with 8; 8 x 5120 18.8 and 17.2. From 4096 tokens on three columns take
+//    two waves, which fill a CU's eight, and two columns of which the second is at most half full
+//    one wave with bf16, whose idle lanes cost the same arithmetic: 2^13 tokens of 8 x 1152 (2.25 columns)
+//    87 with 3, 79 with 2; 2 * 10^4 of 8 x 520 129 with 2, 115 with 1 (fp32 of 8 x 260 52 and 55).
 //  * In the forward four tokens share a block of one column per row (two with n = 8): 3 * 10^4 tokens
 //    of 4 x 504 40.2, alone 41.3; with n = 4 of two columns too: 2 * 10^4 tokens of 4 x 520 46.6, alone
 //    48.6. In the backward they don't: 58.3, shared 61.3.
@@ -3771,9 +3775,14 @@ MixLaunch mix_launch(int64_t B, int64_t nc, int n, bool backward, bool bf16) {
         const bool whole = cols > 14 && cols <= kMixMaxWaves && (!bf16 || alone || (cols == 15 && B >= 8192));
         most = whole ? kMixMaxWaves : 8;
     }
-    if (backward && n == 8) most = 4;
+    if (backward && n == 8) {
+        most = alone ? 8 : 4;
+        if (B >= 4096 && cols == 3) most = 2;
+        if (B >= 4096 && bf16 && nc <= 96) most = 1;
+    }
     const int64_t turns = (cols + most - 1) / most;
-    const int64_t waves = (cols + turns - 1) / turns;
+    // eight waves on one CU are two per SIMD whatever columns they take: no even split needed
+    const int64_t waves = backward && n == 8 && alone ? (cols < most ? cols : most) : (cols + turns - 1) / turns;
     const unsigned tokens = backward || waves > (n == 4 ? 2 : 1) ? 1 : n == 4 ? 4 : 2;
     const int64_t count = (B + tokens - 1) / tokens;
     const int64_t shares = backward ? 1 : (turns < kMixMaxShares ? turns : kMixMaxShares);

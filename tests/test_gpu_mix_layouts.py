@@ -68,11 +68,14 @@ def test_fused_call_outputs(n, h_dtype):
                 assert ((Y.double() - ref)[ok].abs() <= 1e-5 * X.abs().max()).all()
 
 
-# lines that depend on the token count: up to 256 tokens and from 8192 tokens of 15 columns on, 15 and 16
-# columns whole with n = 4
+# lines that depend on the token count: up to 256 tokens (8 waves with n = 8, 15 and 16 columns whole with n = 4),
+# from 4096 tokens with n = 8 (one wave for bf16 rows of at most 96 chunks, two for three columns), from
+# 8192 tokens of 15 columns with n = 4
 TOKEN_LINES = [(n, d, nc, B) for d in (torch.bfloat16, torch.float32)
-               for n, nc, B in [(4, 960, 256), (4, 960, 257), (4, 1024, 256), (4, 1024, 257), (4, 897, 8191),
-                                (4, 897, 8192), (4, 17, 4099), (4, 128, 4101), (4, 129, 4101)]]
+               for n, nc, B in [(8, 320, 256), (8, 320, 257), (8, 577, 256), (8, 96, 4095), (8, 96, 4096), (8, 97, 4096),
+                                (8, 129, 4095), (8, 129, 4096), (8, 192, 4097), (8, 193, 4096), (4, 960, 256),
+                                (4, 960, 257), (4, 1024, 256), (4, 1024, 257), (4, 897, 8191), (4, 897, 8192),
+                                (4, 17, 4099), (4, 128, 4101), (4, 129, 4101)]]
 
 
 @pytest.mark.parametrize("n,dtype,nc,B", TOKEN_LINES, ids=[f"{n}-{str(d)[6:]}-{c}x{b}" for n, d, c, b in TOKEN_LINES])
