@@ -137,12 +137,11 @@ def test_graph_many_launches():
     graph_roundtrip(fn, sets, "16 pairs")
 
 
-# C = 2048 bf16 channels (256 chunks a row) puts the 8-stream kernels on one token per block
-@pytest.mark.parametrize("n,C", [(4, 264), (8, 264), (8, 2048)])
-def test_graph_mix(n, C):
-    say(f"test: graph capture of the residual-mixing pair, {n} streams, C={C}")
-    sets = [list(workloads.mix_streams_device(3001 if C < 1024 else 700, C, 70 + k, "cuda", n))
-            for k in range(N_SETS)]
+# with many tokens the projection and the mixing are two launches, with few of them one
+@pytest.mark.parametrize("n,C,B", [(4, 264, 3001), (8, 264, 3001), (8, 2048, 700), (4, 4096, 96), (8, 4096, 96)])
+def test_graph_mix(n, C, B):
+    say(f"test: graph capture of the residual-mixing pair, {n} streams, C={C}, {B} tokens")
+    sets = [list(workloads.mix_streams_device(B, C, 70 + k, "cuda", n)) for k in range(N_SETS)]
     mfwd, mbwd = (b4.mix_fwd, b4.mix_bwd) if n == 4 else (b4.mix8_fwd, b4.mix8_bwd)
 
     def fn(H, X, G):
