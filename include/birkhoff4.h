@@ -62,7 +62,8 @@ enum {
     BIRKHOFF4_LATENCY = 2     /* four lanes per problem (one row each), no refill */
 };
 
-/* Storage dtypes for inputs (outputs are always fp32; compute is always fp32). */
+/* Storage dtypes: of inputs, and of the outputs that a dtype argument names (dH of the _ex2 and
+ * _ex backwards, the mixed streams); the others are fp32. Compute is always fp32. */
 enum {
     BIRKHOFF4_F32 = 0,
     BIRKHOFF4_BF16 = 1

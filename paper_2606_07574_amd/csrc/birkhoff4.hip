@@ -80,7 +80,7 @@ constexpr float kTiny = 1e-30f;
 // factors of T that are far below fp32 resolution anyway.
 constexpr float kPivMin = 1e-30f;
 constexpr float kFltMin = 1.17549435e-38f;
-constexpr int kMaxSkSteps = 48;   // sk_bwd keeps 2 n floats per lane in LDS
+constexpr int kMaxSkSteps = 48;   // sk_bwd keeps up to 2 n floats per lane in LDS
 constexpr int kSkRegSteps = 20;   // step count whose backward keeps the iterates in VGPRs
 constexpr int kMaxIterCap = 10000;
 // Batches up to this size take the four-lanes-per-problem forward by default.
@@ -1523,7 +1523,9 @@ __global__ __launch_bounds__(mix_short_block(L)) void mix_bwd_short_kernel(const
 
 // sum_j a_j x_j with x_j held by lane j of the quad: a_3 x_3 first, then fused multiply-adds.
 // Written as instructions because the compiler moves each x_j into a register of its own
-// before it multiplies. s_nop 1: a DPP operand may be read two wait states after its write.
+// before it multiplies. s_nop 1: a DPP operand may be read two wait states after its write. The
+// compiler sees no DPP here, so callers must keep the rest of the rules: whole quads active, and no
+// vector write of EXEC (a compare into it) in the five wait states before.
 #define QUAD_PERM(j) " quad_perm:[" #j "," #j "," #j "," #j "] row_mask:0xf bank_mask:0xf\n\t"
 __device__ __forceinline__ float qdot(const float a[4], float x) {
     float r;
@@ -1657,7 +1659,8 @@ __device__ __forceinline__ SkAdjoint sk_adjoint_init(const float A[4], const flo
 // One step back through u^(k) = 1 / max(A v^(k-1), FLT_MIN), v^(k) = 1 / max(A^T u^(k),
 // FLT_MIN): on entry vb holds dL/dv^(k) and, at the last step, ub the direct part of dL/du^(k);
 // on exit vb holds dL/dv^(k-1) and A-bar has gathered both steps' terms. A clamped denominator
-// (an iterate of 2^126) contributes no gradient.
+// contributes no gradient; it is told by its iterate of 2^126, which a denominator of FLT_MIN
+// itself or an ulp above gives too.
 __device__ __forceinline__ void sk_reverse(const float A[4], const float Ac[4], float uk, float vk, float vp, bool last,
                                            SkAdjoint& d) {
     const float bb = vk < kSkClamped ? -d.vb * vk * vk : 0.f;
