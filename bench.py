@@ -5,7 +5,8 @@ One step = one pass of the whole path over the batch: the Newton forward kernel
 (H -> P, dual) followed by the implicit-differentiation backward kernel
 (P, dP -> dH), both launched through the C ABI on torch's current stream. Inputs
 are synthetic (workloads/), generated on the host and resident in HBM before the
-timed region. Prints ONE JSON line.
+timed region. Prints ONE JSON line on stdout, the headline, and before it on stderr
+one line "detail: {...}" with everything else that was measured.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload mix_bf16_b2e24]
 """
@@ -34,6 +35,17 @@ SRC = os.path.join(ROOT, "paper_2606_07574_amd", "csrc", "birkhoff4.hip")
 
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
+
+
+# The line on stdout: short enough for whatever keeps only the end of a program's output.
+HEADLINE_KEYS = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "fwd_proj_per_s",
+                 "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config", "roofline", "path_hbm_frac",
+                 "max_marginal_err")
+
+
+def split_record(out: dict) -> tuple:
+    """(headline, detail) of a full record: the detail keeps every key that the headline leaves out."""
+    return {k: out[k] for k in HEADLINE_KEYS if k in out}, {k: v for k, v in out.items() if k not in HEADLINE_KEYS}
 
 
 def in_bytes(dtype_is_bf16: bool) -> int:
@@ -627,7 +639,9 @@ def main() -> int:
         out["mix_streams"] = bench_mix_streams(args, dev, stream)
         out["mix8_streams"] = bench_mix_streams(args, dev, stream, B=1 << 14, n=8)
 
-    print(json.dumps(out), flush=True)
+    headline, detail = split_record(out)
+    log("detail: " + json.dumps(detail))
+    print(json.dumps(headline), flush=True)
     return 0
 
 
