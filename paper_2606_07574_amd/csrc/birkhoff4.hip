@@ -374,18 +374,20 @@ __global__ __launch_bounds__(kFwdBlock) void newton_fwd_kernel(const void* __res
     if (wv >= nbatch) return;  // uniform across the wave
     // Near the end two of the four groups of four waves (one per SIMD) stop claiming: when all run
     // dry together, four waves per SIMD with a few live lanes each share its issue slots to the
-    // end; staggered, the full waves use the slots that a draining one leaves. The last group
-    // leaves half of the batches that follow each wave's first to the others, the third a quarter,
-    // up to 24 and 14: with fewer batches, fixed counts would leave the block's end to four waves.
-    // Forward without the dual, us, all together / staggered, at 2^20 (64 batches a block), 2^19 (32)
-    // and 4 * 10^5 (25) problems: N(0,1) 32.9 / 31.4, 21.0 / 19.4, 17.4 / 16.7; N(0,10^2) 56.5 / 54.0,
-    // 38.5 / 33.6, 29.9 / 30.2; mixture 44.3 / 41.2, 30.7 / 30.6, 26.3 / 26.8; log-uniform 57.2 / 53.8,
-    // 40.9 / 38.3, 33.9 / 34.2 (a fixed 24, 14 and 6 in three groups: at 4 * 10^5 20.0, 33.9, 26.8 and
-    // 34.6). Slowest against together: N(0,1) at 7.6 * 10^5, 25.2 / 25.9. 3 * 10^6 log-uniform
-    // 121.1 / 118.6; from 2^23 on the same within the runs' 2 %. With the dual, where write requests bound the kernel, it gains
-    // nothing (2^20 of N(0,1) 40.8 / 41.8).
+    // end; staggered, the full waves use the slots that a draining one leaves. Of the batches that
+    // follow each wave's first, the last group leaves half to the others and the third a quarter, up
+    // to 24 and 14 (of fewer than 28 batches 5/8 and 3/8): fixed counts would leave the end of a short
+    // range to four waves. Forward without the dual, us, all together / staggered, at 2^20 (64 batches a
+    // block), 2^19 (32) and 4 * 10^5 (25) problems: N(0,1) 32.9 / 31.4, 21.0 / 19.6, 17.4 / 16.7; N(0,10^2)
+    // 56.5 / 54.0, 38.6 / 34.1, 29.9 / 30.2; mixture 44.3 / 41.2, 30.7 / 28.4, 26.4 / 26.9; log-uniform 57.2 / 53.8,
+    // 40.9 / 37.6, 33.7 / 34.1 (a fixed 24, 14 and 6 in three groups: at 4 * 10^5 20.0, 33.8, 27.0 and
+    // 34.5). Slowest against together: N(0,1) at 7 * 10^5, 24.4 / 25.1. 3 * 10^6 log-uniform 121.1 / 118.6; from
+    // 2^23 on the same within the runs' 2 %. With the dual, where write requests bound the kernel, it
+    // gains nothing (2^20 of N(0,1) 40.8 / 41.8).
     const int spare = nbatch > kFwdWaves ? nbatch - kFwdWaves : 0;
-    const int keep = wv < 8 || WRITE_DUAL ? 0 : wv < 12 ? min(14, spare / 4) : min(24, spare / 2);
+    const int third = spare < 28 ? 3 * spare / 8 : min(14, spare / 4);
+    const int fourth = spare < 28 ? 5 * spare / 8 : min(24, spare / 2);
+    const int keep = wv < 8 || WRITE_DUAL ? 0 : wv < 12 ? third : fourth;
     auto claim = [&]() -> int32_t {
         int32_t v = nbatch;
         if (lane == 0) {

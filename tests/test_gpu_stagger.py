@@ -26,9 +26,9 @@ def same_copies(t, n):
 
 
 # 4 x 4: blocks of one CU share its batches of 64; past sixteen of them, half and a quarter of the
-# rest (at most 24 and 14) are left to the other waves. 16384 problems are one batch per block.
+# rest (at most 24 and 14; 5/8 and 3/8 of fewer than 28) are left to the other waves. 16384 problems are one batch per block.
 @pytest.mark.parametrize("B", [32769, 100003, 16384 * 7 - 1, 16384 * 16, 16384 * 16 + 1, 16384 * 18, 16384 * 20,
-                               16384 * 25, 16384 * 32 + 77, 1 << 20, 16384 * 72 + 5, 3000001])
+                               16384 * 25, 16384 * 32 + 77, 16384 * 43, 16384 * 44, 1 << 20, 16384 * 72 + 5, 3000001])
 def test_projection(B):
     say(f"test: staggered 4x4 forward, B={B}")
     H = np.concatenate([workloads.gauss(401, s, seed=5)[0] for s in (1.0, 10.0, 50.0)])
